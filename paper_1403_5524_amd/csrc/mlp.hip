@@ -28,120 +28,207 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
 const char *set_error(int code, const char *msg);  // defined in rm_api.hip
 
-constexpr int GT = 64;   // output tile edge
-constexpr int GK = 32;   // k chunk
-
-// C[i][j] (ldc) = sum_k A(i,k) B(k,j) + (accumulate ? C : 0)
-// A(i,k) = A[i*sai + k*sak], B(k,j) = B[k*sbk + j*sbj], FP32 in memory.
-template <bool BF16>
-__global__ __launch_bounds__(256) void mlp_gemm_kernel(
-    const float *A, int64_t sai, int64_t sak, const float *B, int64_t sbk,
-    int64_t sbj, float *C, int ldc, int M, int N, int K, int accumulate) {
-  __shared__ float Af[BF16 ? 1 : GT][GK + 1];
-  __shared__ float Bf[BF16 ? 1 : GT][GK + 1];
-  __shared__ __bf16 Ab[BF16 ? GT : 1][GK + 8];
-  __shared__ __bf16 Bb[BF16 ? GT : 1][GK + 8];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int i0 = blockIdx.y * GT, j0 = blockIdx.x * GT;
-  const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
-  const int col = lane & 15, kq = lane >> 4;
-  f4 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += GK) {
-    for (int q = tid; q < GT * GK; q += 256) {
-      const int r = q / GK, k = q % GK;
-      const int gi = i0 + r, gj = j0 + r, gk = k0 + k;
-      const float av = (gi < M && gk < K) ? A[gi * sai + gk * sak] : 0.f;
-      const float bv = (gj < N && gk < K) ? B[gk * sbk + gj * sbj] : 0.f;
-      if (BF16) {
-        Ab[r][k] = (__bf16)av;
-        Bb[r][k] = (__bf16)bv;
-      } else {
-        Af[r][k] = av;
-        Bf[r][k] = bv;
-      }
-    }
-    __syncthreads();
-    if (BF16) {
-      bf8 a[2], b[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        a[t] = *(const bf8 *)&Ab[wi + 16 * t + col][8 * kq];
-        b[t] = *(const bf8 *)&Bb[wj + 16 * t + col][8 * kq];
-      }
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-          acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], b[y],
-                                                              acc[x][y], 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < GK; kk += 4) {
-        float a[2], b[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          a[t] = Af[wi + 16 * t + col][kk + kq];
-          b[t] = Bf[wj + 16 * t + col][kk + kq];
-        }
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-          for (int y = 0; y < 2; ++y)
-            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[x], b[y],
-                                                             acc[x][y], 0, 0, 0);
-      }
-    }
-    __syncthreads();
-  }
-  // D[i][j]: j = lane%16, i = 4*(lane/16) + r
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < 2; ++y)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int gi = i0 + wi + 16 * x + 4 * kq + r;
-        const int gj = j0 + wj + 16 * y + col;
-        if (gi < M && gj < N) {
-          float *c = C + (int64_t)gi * ldc + gj;
-          *c = (accumulate ? *c : 0.f) + acc[x][y][r];
-        }
-      }
-}
-
 __device__ inline float sigm(float x) { return 1.f / (1.f + expf(-x)); }
 
-// Z[b][j] += bias[j]; A = silu(Z) (act) or copy
-__global__ void bias_act_kernel(float *Z, float *A, const float *bias, int B,
-                                int N, int act) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)B * N) return;
-  const float z = Z[idx] + bias[idx % N];
-  Z[idx] = z;
-  A[idx] = act ? z * sigm(z) : z;
+// What a product's result goes through on its way out.
+enum { EPI_FORWARD, EPI_BACKWARD, EPI_WEIGHTS };
+
+// One product C = A B of a layer, FP32 in memory.  Operands are stored with
+// the summed index k contiguous, X[row * ld + k], or (transposed) with the
+// row contiguous, X[k * ld + row].
+struct MlpProduct {
+  const float *A, *B;
+  int lda, ldb;
+  int M, N, K;
+  const float *bias;  // forward: b_l
+  float *Z, *out;     // forward: pre-activations; the result
+  const float *Zin;   // backward: pre-activations of the layer below
+  float *db;          // weights: the bias gradient, sum over k of A's rows
+  int act;            // forward: SiLU, else linear
+};
+
+// Eight consecutive k of one operand row for this lane, zero from K on.
+// `whole` (uniform): the 32-wide chunk ends at or before K.
+// (The compiler joins the contiguous ones into 16-byte loads, which need no
+// alignment here.)
+template <bool TR>
+__device__ __forceinline__ void mlp_load(float (&x)[8], const float *X, int ld,
+                                         int row, int k, int K, bool whole) {
+  if (whole) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      x[q] = TR ? X[(int64_t)(k + q) * ld + row] : X[(int64_t)row * ld + k + q];
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      x[q] = k + q >= K ? 0.f
+             : TR       ? X[(int64_t)(k + q) * ld + row]
+                        : X[(int64_t)row * ld + k + q];
+  }
 }
 
-// dZ = dA * silu'(Z)
-__global__ void act_bwd_kernel(const float *dA, const float *Z, float *dZ,
-                               int64_t count) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= count) return;
-  const float z = Z[idx];
-  const float s = sigm(z);
-  dZ[idx] = dA[idx] * s * (1.f + z * (1.f - s));
-}
-
-// db[j] = sum_b dZ[b][j]
-__global__ void bias_grad_kernel(const float *dZ, float *db, int B, int N) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
-  float s = 0.f;
-  for (int b = 0; b < B; ++b) s += dZ[(int64_t)b * N + j];
-  db[j] = s;
+// The layers are small (a 256-wide layer of 1024 samples is 0.13 GFLOP on
+// 2 MB that sit in L2), so a product is bound by its chain of loads and by
+// launches, not by the matrix cores.  Operands therefore go from L2 to the
+// fragment registers without LDS or barriers, G chunks of 32 k at a time and
+// the next group in flight during the products; tiles are small enough that
+// such a layer fills the chip, and everything elementwise rides on the
+// product: bias and activation (forward), the activation's derivative
+// (backward), the bias gradient (weights).  Through LDS with a barrier pair
+// per 32 k and scalar strided loads a product took 48 us, and the bias
+// gradient, one thread per column, 178 us; a step of 16 -> 256 -> 256 -> 256
+// -> 1 with 1024 samples took 1280 us and takes 74 us.
+//
+// A wavefront holds 16 F x 16 F of the result.  Forward and backward: 2 x 2
+// wavefronts, each summing all of K in steps of 32 in ascending order.
+// Weights: K is the batch, the longest index, and the result the smallest,
+// so the block's KW wavefronts split K and add their parts in LDS in a fixed
+// order.  The bias gradient sums A's FP32 values before they are rounded.
+template <bool BF16, int EPI, int F, int KW>
+__global__ __launch_bounds__(EPI == EPI_WEIGHTS ? 64 * KW : 256) void mlp_product_kernel(
+    MlpProduct p) {
+  constexpr bool TA = EPI == EPI_WEIGHTS, TB = EPI != EPI_FORWARD;
+  constexpr int G = F == 1 ? 4 : 2, WQ = EPI == EPI_WEIGHTS ? 1 : 2;
+  constexpr int TW = 16 * F;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, kq = lane >> 4;
+  const int i0 = (blockIdx.y * WQ + (WQ == 2 ? wave >> 1 : 0)) * TW;
+  const int j0 = (blockIdx.x * WQ + (WQ == 2 ? wave & 1 : 0)) * TW;
+  // this wavefront's k: all, or its share in whole chunks
+  int kb = 0, ke = p.K;
+  if (EPI == EPI_WEIGHTS) {
+    const int per = ((p.K + 31) / 32 + KW - 1) / KW * 32;
+    kb = min(p.K, wave * per);
+    ke = min(p.K, kb + per);
+  }
+  // rows past the edge read the last one; what they give is not stored
+  int ri[F], rj[F];
+#pragma unroll
+  for (int t = 0; t < F; ++t) {
+    ri[t] = min(i0 + 16 * t + col, p.M - 1);
+    rj[t] = min(j0 + 16 * t + col, p.N - 1);
+  }
+  f4 acc[F][F];
+  float rs[F];
+#pragma unroll
+  for (int x = 0; x < F; ++x) {
+    rs[x] = 0.f;
+#pragma unroll
+    for (int y = 0; y < F; ++y) acc[x][y] = f4{0.f, 0.f, 0.f, 0.f};
+  }
+  float a[G][F][8], b[G][F][8], an[G][F][8], bn[G][F][8];
+  auto load = [&](float (&u)[G][F][8], float (&v)[G][F][8], int k0) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int kc = k0 + 32 * g;
+      const bool whole = kc + 32 <= ke;
+#pragma unroll
+      for (int t = 0; t < F; ++t) {
+        mlp_load<TA>(u[g][t], p.A, p.lda, ri[t], kc + 8 * kq, ke, whole);
+        mlp_load<TB>(v[g][t], p.B, p.ldb, rj[t], kc + 8 * kq, ke, whole);
+      }
+    }
+  };
+  if (kb < ke) load(a, b, kb);
+  for (int k0 = kb; k0 < ke; k0 += 32 * G) {
+    if (k0 + 32 * G < ke) load(an, bn, k0 + 32 * G);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (k0 + 32 * g >= ke) break;
+      if (EPI == EPI_WEIGHTS) {
+#pragma unroll
+        for (int t = 0; t < F; ++t)
+#pragma unroll
+          for (int q = 0; q < 8; ++q) rs[t] += a[g][t][q];
+      }
+      if (BF16) {
+        bf8 af[F], bf[F];
+#pragma unroll
+        for (int t = 0; t < F; ++t)
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            af[t][q] = (__bf16)a[g][t][q];
+            bf[t][q] = (__bf16)b[g][t][q];
+          }
+#pragma unroll
+        for (int x = 0; x < F; ++x)
+#pragma unroll
+          for (int y = 0; y < F; ++y)
+            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                af[x], bf[y], acc[x][y], 0, 0, 0);
+      } else {
+        // step q takes k = 8 kq + q of every lane
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+          for (int x = 0; x < F; ++x)
+#pragma unroll
+            for (int y = 0; y < F; ++y)
+              acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                  a[g][x][q], b[g][y][q], acc[x][y], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int t = 0; t < F; ++t)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          a[g][t][q] = an[g][t][q];
+          b[g][t][q] = bn[g][t][q];
+        }
+  }
+  // D[i][j]: j = lane % 16, i = 4 (lane / 16) + r
+  if constexpr (EPI == EPI_WEIGHTS) {
+    __shared__ float part[KW][F * F * 4][64];
+    __shared__ float rows[KW][F][64];
+#pragma unroll
+    for (int x = 0; x < F; ++x) {
+      rows[wave][x][lane] = rs[x];
+#pragma unroll
+      for (int y = 0; y < F; ++y)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wave][(x * F + y) * 4 + r][lane] = acc[x][y][r];
+    }
+    __syncthreads();
+    for (int q = tid; q < F * F * 256; q += 64 * KW) {
+      const int f = q >> 6, ln = q & 63, r = f & 3, y = (f >> 2) % F, x = (f >> 2) / F;
+      const int gi = i0 + 16 * x + 4 * (ln >> 4) + r, gj = j0 + 16 * y + (ln & 15);
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < KW; ++w) s += part[w][f][ln];
+      if (gi < p.M && gj < p.N) p.out[(int64_t)gi * p.N + gj] = s;
+    }
+    if (blockIdx.x == 0 && tid < TW && i0 + tid < p.M) {
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < KW; ++w)
+#pragma unroll
+        for (int h = 0; h < 4; ++h) s += rows[w][tid >> 4][16 * h + (tid & 15)];
+      p.db[i0 + tid] = s;
+    }
+  } else {
+#pragma unroll
+    for (int x = 0; x < F; ++x)
+#pragma unroll
+      for (int y = 0; y < F; ++y)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int gi = i0 + 16 * x + 4 * kq + r, gj = j0 + 16 * y + col;
+          if (gi >= p.M || gj >= p.N) continue;
+          const int64_t o = (int64_t)gi * p.N + gj;
+          if (EPI == EPI_FORWARD) {
+            const float z = acc[x][y][r] + p.bias[gj];
+            p.Z[o] = z;
+            p.out[o] = p.act ? z * sigm(z) : z;
+          } else {
+            // dZ = dA silu'(Z)
+            const float z = p.Zin[o], s = sigm(z);
+            p.out[o] = acc[x][y][r] * s * (1.f + z * (1.f - s));
+          }
+        }
+  }
 }
 
 // MSE: loss = mean (y - t)^2, dY = 2 (y - t) / B; one workgroup
@@ -249,16 +336,27 @@ struct Mlp {
 
 static unsigned g1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-static void gemm(const Mlp &q, const float *A, int64_t sai, int64_t sak,
-                 const float *B, int64_t sbk, int64_t sbj, float *C, int ldc,
-                 int M, int N, int K, int acc, hipStream_t st) {
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
+// Launch of a product.  A block's result is 32 x 32 (weights: 16 x 16) while
+// that gives up to 1024 blocks, four per CU; beyond, four times as large,
+// which halves what each multiply reads.
+template <bool BF16, int EPI, int F>
+static void launch_product(const MlpProduct &p, hipStream_t st) {
+  constexpr int KW = 8, T = EPI == EPI_WEIGHTS ? 16 * F : 32 * F;
+  const dim3 grid((p.N + T - 1) / T, (p.M + T - 1) / T);
+  hipLaunchKernelGGL((mlp_product_kernel<BF16, EPI, F, KW>), grid,
+                     dim3(EPI == EPI_WEIGHTS ? 64 * KW : 256), 0, st, p);
+}
+
+template <int EPI>
+static void product(const Mlp &q, const MlpProduct &p, hipStream_t st) {
+  constexpr int T = EPI == EPI_WEIGHTS ? 16 : 32;
+  const int64_t blocks = (int64_t)((p.N + T - 1) / T) * ((p.M + T - 1) / T);
   if (q.prec == 0)
-    hipLaunchKernelGGL(mlp_gemm_kernel<true>, grid, dim3(256), 0, st, A, sai,
-                       sak, B, sbk, sbj, C, ldc, M, N, K, acc);
+    blocks <= 1024 ? launch_product<true, EPI, 1>(p, st)
+                   : launch_product<true, EPI, 2>(p, st);
   else
-    hipLaunchKernelGGL(mlp_gemm_kernel<false>, grid, dim3(256), 0, st, A, sai,
-                       sak, B, sbk, sbj, C, ldc, M, N, K, acc);
+    blocks <= 1024 ? launch_product<false, EPI, 1>(p, st)
+                   : launch_product<false, EPI, 2>(p, st);
 }
 
 static int ensure_cap(Mlp &q, int B) {
@@ -281,40 +379,51 @@ static int ensure_cap(Mlp &q, int B) {
 // of its slot); the input is X.
 static void forward(Mlp &q, const float *X, int B, hipStream_t st) {
   const float *in = X;
-  int64_t ld_in = q.d_in;
   for (int l = 0; l < q.layers; ++l) {
-    float *Z = q.Z + (int64_t)l * B * q.width;
-    float *A = q.A + (int64_t)l * B * q.width;
-    const int N = q.dout[l], K = q.din[l];
-    // Z[b][j] = sum_k in[b][k] W[j][k]
-    gemm(q, in, ld_in, 1, q.p + q.woff[l], 1, K, Z, N, B, N, K, 0, st);
-    const int act = (l + 1 < q.layers) ? 1 : 0;
-    hipLaunchKernelGGL(bias_act_kernel, dim3(g1((int64_t)B * N)), dim3(256), 0,
-                       st, Z, A, q.p + q.boff[l], B, N, act);
-    in = A;
-    ld_in = N;
+    MlpProduct p{};
+    // Z[b][j] = sum_k in[b][k] W[j][k] + b[j]
+    p.A = in;
+    p.B = q.p + q.woff[l];
+    p.lda = p.ldb = p.K = q.din[l];
+    p.M = B;
+    p.N = q.dout[l];
+    p.bias = q.p + q.boff[l];
+    p.Z = q.Z + (int64_t)l * B * q.width;
+    p.out = q.A + (int64_t)l * B * q.width;
+    p.act = (l + 1 < q.layers) ? 1 : 0;
+    product<EPI_FORWARD>(q, p, st);
+    in = p.out;
   }
 }
 
 static void backward(Mlp &q, const float *X, int B, const float *dY,
                      hipStream_t st) {
-  // dZ of the last layer is dY (linear output)
+  // dZ of the last layer is dY (linear output); below, two buffers in turn
   const float *dZ = dY;
   for (int l = q.layers - 1; l >= 0; --l) {
     const int N = q.dout[l], K = q.din[l];
-    const float *in = (l == 0) ? X : q.A + (int64_t)(l - 1) * B * q.width;
-    const int64_t ld_in = (l == 0) ? q.d_in : q.width;
-    // dW[j][k] = sum_b dZ[b][j] in[b][k]
-    gemm(q, dZ, 1, N, in, ld_in, 1, q.g + q.woff[l], K, N, K, B, 0, st);
-    hipLaunchKernelGGL(bias_grad_kernel, dim3(g1(N)), dim3(256), 0, st, dZ,
-                       q.g + q.boff[l], B, N);
+    // dW[j][k] = sum_b dZ[b][j] in[b][k], db[j] = sum_b dZ[b][j]
+    MlpProduct w{};
+    w.A = dZ;
+    w.lda = w.M = N;
+    w.B = (l == 0) ? X : q.A + (int64_t)(l - 1) * B * q.width;
+    w.ldb = w.N = K;
+    w.K = B;
+    w.out = q.g + q.woff[l];
+    w.db = q.g + q.boff[l];
+    product<EPI_WEIGHTS>(q, w, st);
     if (l == 0) break;
-    // dA_{l-1}[b][k] = sum_j dZ[b][j] W[j][k]
-    gemm(q, dZ, N, 1, q.p + q.woff[l], K, 1, q.dA, K, B, K, N, 0, st);
-    hipLaunchKernelGGL(act_bwd_kernel, dim3(g1((int64_t)B * K)), dim3(256), 0,
-                       st, q.dA, q.Z + (int64_t)(l - 1) * B * q.width, q.dZ,
-                       (int64_t)B * K);
-    dZ = q.dZ;
+    // dZ_{l-1}[b][k] = silu'(Z_{l-1}[b][k]) sum_j dZ[b][j] W[j][k]
+    MlpProduct a{};
+    a.A = dZ;
+    a.lda = a.K = N;
+    a.B = q.p + q.woff[l];
+    a.ldb = a.N = K;
+    a.M = B;
+    a.Zin = q.Z + (int64_t)(l - 1) * B * q.width;
+    a.out = (l & 1) ? q.dZ : q.dA;
+    product<EPI_BACKWARD>(q, a, st);
+    dZ = a.out;
   }
 }
 
