@@ -161,7 +161,6 @@ __global__ void inner_init_kernel(double *A, double *V, int D, int Dp,
 // |G_pq| <= tol sqrt(G_pp G_qq) leaves all columns mutually orthogonal.
 constexpr int BJ_B = 16;        // columns per block
 constexpr int BJ_W = 2 * BJ_B;  // columns per block pair
-constexpr int BJ_CH = 256;      // rows per rotation workgroup (4 waves x 64)
 constexpr int BJ_MAXCH = 16;    // row chunks of the Gram kernel, at most
 constexpr int BJ_DMAX = 16384;  // largest dimension
 
@@ -240,6 +239,22 @@ __device__ inline void bj_pair32(int r, int kk, int &p, int &q) {
   }
 }
 
+// The rotation of a column pair with Gram entries al, be, ga: the smaller
+// root of t^2 + 2 zeta t - 1 = 0, zeta = d / (2 ga), as sign(d) 2 ga / (|d| +
+// sqrt(d^2 + 4 ga^2)).
+__device__ __forceinline__ void bj_rotation(double al, double be, double ga,
+                                            double tol, double &c, double &s) {
+  c = 1.0;
+  s = 0.0;
+  if (ga * ga > tol * tol * (al * be)) {
+    const double d = be - al;
+    const double tt = (d >= 0.0 ? 2.0 * ga : -2.0 * ga) /
+                      (fabs(d) + sqrt(d * d + 4.0 * ga * ga));
+    c = rsqrt(1.0 + tt * tt);
+    s = c * tt;
+  }
+}
+
 // One workgroup per block pair: sums the partial Grams, and if any column
 // pair fails the orthogonality test, applies one cyclic sweep of two-sided
 // Jacobi to G accumulating U; else marks the pair skipped.  (One sweep per
@@ -247,18 +262,26 @@ __device__ inline void bj_pair32(int r, int kk, int &p, int &q) {
 // the outer sweeps revisit every pair anyway.)  A round applies 16
 // disjoint rotations J (pair (p, q): column p' = c p - s q, q' = s p + c q);
 // G' = J^T G J maps each 2 x 2 block (rows of pair a, columns of pair b)
-// from its own four entries, so thread a * 16 + b updates one block in
-// place and the rotated pair's off-diagonal is set to zero.  Counts the
-// block pairs rotated.
+// from its own four entries, so thread a * 16 + b maps one block, and the
+// rotated pair's off-diagonal is set to zero.  Counts the block pairs
+// rotated.
+//
+// The 31 rounds are a serial chain.  G and U go back and forth between two
+// LDS copies, and every thread forms both rotations that it needs, so a
+// round is one step of loads, rotations, products and stores with one
+// barrier (25 us at 32 block pairs; 27 us with 16 threads forming the
+// rotations for the others and G updated in place, two barriers a round).
+// What is left is the rotations' arithmetic and the LDS traffic of G and U.
 __global__ __launch_bounds__(256) void bj_eig_kernel(
     const double *__restrict__ part, int nchunk, double tol,
     double *__restrict__ Uout, int *__restrict__ skip, int *__restrict__ cnt) {
-  __shared__ double G[BJ_W][BJ_W + 1];
-  __shared__ double U[BJ_W][BJ_W + 1];
-  __shared__ double cs[16][2];
+  __shared__ double G2[2][BJ_W][BJ_W + 1];
+  __shared__ double U2[2][BJ_W][BJ_W + 1];
   __shared__ int need;
   const int k = blockIdx.x, tid = threadIdx.x;
   const double *pk = part + (int64_t)k * nchunk * 768;
+  auto &G = G2[0];
+  auto &U = U2[0];
   if (tid == 0) need = 0;
   for (int e = tid; e < 768; e += 256) {
     // every chunk's partial in flight at once (nchunk <= BJ_MAXCH; addresses
@@ -293,79 +316,55 @@ __global__ __launch_bounds__(256) void bj_eig_kernel(
     if (tid == 0) skip[k] = 1;
     return;
   }
-  const int ka = tid >> 4, kb = tid & 15;  // this thread's 2 x 2 block of G
-  {
-    for (int r = 0; r < 31; ++r) {
-      if (tid < 16) {
-        int p, q;
-        bj_pair32(r, tid, p, q);
-        const double al = G[p][p], be = G[q][q], ga = G[p][q];
-        double c = 1.0, s = 0.0;
-        if (ga * ga > tol * tol * (al * be)) {
-          // the smaller root of t^2 + 2 zeta t - 1 = 0, zeta = d / (2 ga),
-          // as sign(d) 2 ga / (|d| + sqrt(d^2 + 4 ga^2)): one square root
-          // and one division
-          const double d = be - al;
-          const double tt = (d >= 0.0 ? 2.0 * ga : -2.0 * ga) /
-                            (fabs(d) + sqrt(d * d + 4.0 * ga * ga));
-          c = rsqrt(1.0 + tt * tt);
-          s = c * tt;
-        }
-        cs[tid][0] = c;
-        cs[tid][1] = s;
-      }
-      __syncthreads();
-      {
-        const double ca = cs[ka][0], sa = cs[ka][1];
-        const double cb = cs[kb][0], sb = cs[kb][1];
-        if (sa != 0.0 || sb != 0.0) {
-          int p, q, u, v;
-          bj_pair32(r, ka, p, q);
-          bj_pair32(r, kb, u, v);
-          const double gpu = G[p][u], gpv = G[p][v], gqu = G[q][u], gqv = G[q][v];
-          // columns: (u, v) -> (cb u - sb v, sb u + cb v)
-          const double hpu = cb * gpu - sb * gpv, hpv = sb * gpu + cb * gpv;
-          const double hqu = cb * gqu - sb * gqv, hqv = sb * gqu + cb * gqv;
-          // rows: (p, q) -> (ca p - sa q, sa p + ca q)
-          G[p][u] = ca * hpu - sa * hqu;
-          G[q][u] = sa * hpu + ca * hqu;
-          G[p][v] = ca * hpv - sa * hqv;
-          G[q][v] = sa * hpv + ca * hqv;
-          if (ka == kb && sa != 0.0) {
-            G[p][v] = 0.0;
-            G[q][u] = 0.0;
-          }
-        }
-      }
-      for (int e = tid; e < BJ_W * 16; e += 256) {
-        const int i = e >> 4, kk = e & 15;
-        const double s = cs[kk][1];
-        if (s != 0.0) {
-          const double c = cs[kk][0];
-          int p, q;
-          bj_pair32(r, kk, p, q);
-          const double x = U[i][p], y = U[i][q];
-          U[i][p] = c * x - s * y;
-          U[i][q] = s * x + c * y;
-        }
-      }
-      __syncthreads();
-    }
+  // this thread's 2 x 2 block of G; its U entries are column pair kb of rows
+  // ka and ka + 16
+  const int ka = tid >> 4, kb = tid & 15;
+#pragma unroll 1
+  for (int r = 0; r < 31; ++r) {
+    const auto &Gi = G2[r & 1], &Ui = U2[r & 1];
+    auto &Go = G2[(r + 1) & 1], &Uo = U2[(r + 1) & 1];
+    int p, q, u, v;
+    bj_pair32(r, ka, p, q);
+    bj_pair32(r, kb, u, v);
+    const double app = Gi[p][p], aqq = Gi[q][q], apq = Gi[p][q];
+    const double buu = Gi[u][u], bvv = Gi[v][v], buv = Gi[u][v];
+    const double gpu = Gi[p][u], gpv = Gi[p][v], gqu = Gi[q][u], gqv = Gi[q][v];
+    const double x0 = Ui[ka][u], y0 = Ui[ka][v];
+    const double x1 = Ui[ka + 16][u], y1 = Ui[ka + 16][v];
+    double ca, sa, cb, sb;
+    bj_rotation(app, aqq, apq, tol, ca, sa);
+    bj_rotation(buu, bvv, buv, tol, cb, sb);
+    // columns: (u, v) -> (cb u - sb v, sb u + cb v)
+    const double hpu = cb * gpu - sb * gpv, hpv = sb * gpu + cb * gpv;
+    const double hqu = cb * gqu - sb * gqv, hqv = sb * gqu + cb * gqv;
+    // rows: (p, q) -> (ca p - sa q, sa p + ca q)
+    const bool zero = ka == kb && sa != 0.0;
+    Go[p][u] = ca * hpu - sa * hqu;
+    Go[q][u] = zero ? 0.0 : sa * hpu + ca * hqu;
+    Go[p][v] = zero ? 0.0 : ca * hpv - sa * hqv;
+    Go[q][v] = sa * hpv + ca * hqv;
+    Uo[ka][u] = cb * x0 - sb * y0;
+    Uo[ka][v] = sb * x0 + cb * y0;
+    Uo[ka + 16][u] = cb * x1 - sb * y1;
+    Uo[ka + 16][v] = sb * x1 + cb * y1;
+    __syncthreads();
   }
   double *uo = Uout + (int64_t)k * BJ_W * BJ_W;
-  for (int e = tid; e < BJ_W * BJ_W; e += 256) uo[e] = U[e >> 5][e & 31];
+  for (int e = tid; e < BJ_W * BJ_W; e += 256) uo[e] = U2[1][e >> 5][e & 31];
   if (tid == 0) {
     skip[k] = 0;
     atomicAdd(cnt, 1);
   }
 }
 
-// X <- X U for the 32 columns of block pair blockIdx.x, in A and in V, over
-// the rows of chunk blockIdx.y (in place: each wave loads its 16-row group
-// of all 32 columns before writing it back).  Computed as Y^T = U^T X^T so
-// that a lane's outputs run down a column: A operand U[4 s + kq][16 it +
-// col], B operand X[row0 + col][position 4 s + kq], output lane r holds
-// Y[row0 + col][position 16 it + kq + 4 r].
+// X <- X U for the 32 columns of block pair blockIdx.x, in A (blockIdx.z 0)
+// or V (1), over the rows of chunk blockIdx.y, 16 GW rows per wave (in place:
+// each wave loads its 16-row group of all 32 columns before writing it
+// back).  Computed as Y^T = U^T X^T so that a lane's outputs run down a
+// column: A operand U[4 s + kq][16 it + col], B operand X[row0 +
+// col][position 4 s + kq], output lane r holds Y[row0 + col][position
+// 16 it + kq + 4 r].
+template <int GW>
 __global__ __launch_bounds__(256) void bj_rotate_kernel(
     double *A, double *V, int Dp, int nb, int t,
     const double *__restrict__ Uall, const int *__restrict__ skip) {
@@ -375,6 +374,7 @@ __global__ __launch_bounds__(256) void bj_rotate_kernel(
   const int col = lane & 15, kq = lane >> 4;
   int P, Qb;
   bj_pair(nb, t, k, P, Qb);
+  double *X = blockIdx.z ? V : A;
   const double *Uk = Uall + (int64_t)k * BJ_W * BJ_W;
   double ua[2][8];
 #pragma unroll
@@ -389,30 +389,43 @@ __global__ __launch_bounds__(256) void bj_rotate_kernel(
     cout0[r] = (int64_t)bj_col(P, Qb, kq + 4 * r) * Dp;
     cout1[r] = (int64_t)bj_col(P, Qb, BJ_B + kq + 4 * r) * Dp;
   }
-  const int rbeg = c * BJ_CH + wave * 64;
+  const int rbeg = (4 * c + wave) * 16 * GW;
 #pragma unroll
-  for (int mat = 0; mat < 2; ++mat) {
-    double *X = mat ? V : A;
+  for (int g = 0; g < GW; ++g) {
+    const int row0 = rbeg + 16 * g;
+    if (row0 >= Dp) break;
+    double xb[8];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int row0 = rbeg + 16 * g;
-      if (row0 >= Dp) break;
-      double xb[8];
+    for (int s = 0; s < 8; ++s) xb[s] = X[cin[s] + row0 + col];
+    d4 y0 = {0.0, 0.0, 0.0, 0.0}, y1 = y0;
 #pragma unroll
-      for (int s = 0; s < 8; ++s) xb[s] = X[cin[s] + row0 + col];
-      d4 y0 = {0.0, 0.0, 0.0, 0.0}, y1 = y0;
+    for (int s = 0; s < 8; ++s) {
+      y0 = __builtin_amdgcn_mfma_f64_16x16x4f64(ua[0][s], xb[s], y0, 0, 0, 0);
+      y1 = __builtin_amdgcn_mfma_f64_16x16x4f64(ua[1][s], xb[s], y1, 0, 0, 0);
+    }
 #pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        y0 = __builtin_amdgcn_mfma_f64_16x16x4f64(ua[0][s], xb[s], y0, 0, 0, 0);
-        y1 = __builtin_amdgcn_mfma_f64_16x16x4f64(ua[1][s], xb[s], y1, 0, 0, 0);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        X[cout0[r] + row0 + col] = y0[r];
-        X[cout1[r] + row0 + col] = y1[r];
-      }
+    for (int r = 0; r < 4; ++r) {
+      X[cout0[r] + row0 + col] = y0[r];
+      X[cout1[r] + row0 + col] = y1[r];
     }
   }
+}
+
+// Rotations of a round.  Four row groups a wave share the loads of U; one a
+// wave, with four times the wavefronts, where four would leave fewer than
+// four workgroups per CU (dimension 1024: 8.1 us a round against 10.2 with
+// four groups and both matrices per wave).
+static void launch_rotate(double *A, double *V, int Dp, int nb, int t,
+                          const double *U, const int *skip, hipStream_t st) {
+  const int npair = nb / 2;
+  auto go = [&](auto kern, int rows) {
+    hipLaunchKernelGGL(kern, dim3(npair, (Dp + rows - 1) / rows, 2), dim3(256), 0,
+                       st, A, V, Dp, nb, t, U, skip);
+  };
+  if ((int64_t)npair * 2 * ((Dp + 255) / 256) >= 1024)
+    go(bj_rotate_kernel<4>, 256);
+  else
+    go(bj_rotate_kernel<1>, 64);
 }
 
 // Column k after convergence: a_k = (H + sigma I) v_k.  Eigenvalue by the
@@ -524,7 +537,7 @@ int rm_inner_region(const rm_inner_desc *d, double *E_pole, double *w,
     return in_fail(RM_ERR_ARG, std::string(fn) + ": quadrature table n_chan^2 n_quad over 8 GB");
   hipStream_t st = (hipStream_t)stream;
   const int D = n * N, Dp = (D + BJ_W - 1) / BJ_W * BJ_W;  // even block count
-  const int nb = Dp / BJ_B, npair = nb / 2, nchunk = (Dp + BJ_CH - 1) / BJ_CH;
+  const int nb = Dp / BJ_B, npair = nb / 2;
   // Gram chunks: 64-row multiples, at most BJ_MAXCH of them (the eigen
   // kernel loads every chunk's partial at once)
   const int gram_rows = 64 * ((Dp + 64 * BJ_MAXCH - 1) / (64 * BJ_MAXCH));
@@ -611,8 +624,7 @@ int rm_inner_region(const rm_inner_desc *d, double *E_pole, double *w,
                            nb, t, gchunk, gram_rows, part);
         hipLaunchKernelGGL(bj_eig_kernel, dim3(npair), dim3(256), 0, st, part, gchunk,
                            tol, Ub, skip, cnt);
-        hipLaunchKernelGGL(bj_rotate_kernel, dim3(npair, nchunk), dim3(256), 0, st, A, V,
-                           Dp, nb, t, Ub, skip);
+        launch_rotate(A, V, Dp, nb, t, Ub, skip, st);
         hip_ok(hipGetLastError());
       }
     }
