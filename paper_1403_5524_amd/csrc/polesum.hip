@@ -10,13 +10,12 @@
 // written from the same accumulators.
 //
 // Items come from a table built on the host (largest symmetries first).
-// Without a counter, block b runs item (b mod 8) * ceil(N/8) + b / 8, so
-// consecutive items -- the same W tiles for successive energy groups -- land
-// on the same XCD (blocks are dispatched round-robin over the 8 XCDs) and
-// share its L2.  With a counter the grid is persistent and pulls items.
+// Block b runs item (b mod 8) * ceil(N/8) + b / 8, so consecutive items --
+// the same W tiles for successive energy groups -- land on the same XCD
+// (blocks are dispatched round-robin over the 8 XCDs) and share its L2.
 #include <algorithm>
 
-#include "rm_internal.h"
+#include "polesum_group.h"
 
 namespace rmx {
 
@@ -33,7 +32,8 @@ struct F64Smem {  // two stages: one feeds the MFMAs while the next fills
   double Ds[2][PS_EG][PS_KC];
 };
 
-// One work item: tile pair (I, J), J >= I, for PS_EG energies.  MASK bit
+// One work item: tile pair (I, J), J >= I, for the energies of [elo, ehi)
+// among the PS_EG from e0 on.  MASK bit
 // 2 a + b says whether the 16 x 16 output block (a, b) of the 32 x 32 tile
 // holds any element that is kept (row and column below n, row <= column on
 // a diagonal tile); the others are never formed.  Diagonal tiles are
@@ -53,14 +53,13 @@ __device__ inline double ps_weight(double ep, double gm, double e) {
 }
 
 template <int MASK, int PART>
-__device__ void ps_f64_item_m(const SymDev &S, int I, int J, int grp,
-                              const double *__restrict__ E, int m,
+__device__ __forceinline__ void ps_f64_item_m(const SymDev &S, int I, int J, int e0, int elo,
+                              int ehi, const double *__restrict__ E,
                               double *__restrict__ Rbase, int64_t estride,
                               int ld, F64Smem &sm) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int e0 = grp * PS_EG;
   constexpr bool diag = !(MASK & 4);
   const int n_pad = S.n_pad;
 
@@ -77,7 +76,7 @@ __device__ void ps_f64_item_m(const SymDev &S, int I, int J, int grp,
     de[u] = idx / PS_KC;
     dk[u] = idx % PS_KC;
     const int e = e0 + de[u];
-    ev[u] = e < m;
+    ev[u] = e >= elo && e < ehi;
     Eloc[u] = ev[u] ? E[e] : 0.0;
   }
 
@@ -178,7 +177,7 @@ __device__ void ps_f64_item_m(const SymDev &S, int I, int J, int grp,
 #pragma unroll
   for (int e = 0; e < PS_EW; ++e) {
     const int eg = e0 + wave * PS_EW + e;
-    if (eg >= m) continue;
+    if (eg < elo || eg >= ehi) continue;
     double *Re = Rbase + (int64_t)eg * estride;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -201,21 +200,21 @@ __device__ void ps_f64_item_m(const SymDev &S, int I, int J, int grp,
 }
 
 template <int PART>
-__device__ void ps_f64_item(const SymDev &S, int I, int J, int grp,
-                            const double *__restrict__ E, int m,
+__device__ __forceinline__ void ps_f64_item(const SymDev &S, int I, int J, int e0, int elo,
+                            int ehi, const double *__restrict__ E,
                             double *__restrict__ Rbase, int64_t estride,
                             int ld, F64Smem &sm) {
   // the last tile may reach at most 16 rows past n (n_pad = 32 ceil(n/32))
   if (I == J) {
     if (S.n - I * PS_T <= 16)
-      ps_f64_item_m<1, PART>(S, I, J, grp, E, m, Rbase, estride, ld, sm);
+      ps_f64_item_m<1, PART>(S, I, J, e0, elo, ehi, E, Rbase, estride, ld, sm);
     else
-      ps_f64_item_m<1 | 2 | 8, PART>(S, I, J, grp, E, m, Rbase, estride, ld, sm);
+      ps_f64_item_m<1 | 2 | 8, PART>(S, I, J, e0, elo, ehi, E, Rbase, estride, ld, sm);
   } else {
     if (S.n - J * PS_T <= 16)
-      ps_f64_item_m<1 | 4, PART>(S, I, J, grp, E, m, Rbase, estride, ld, sm);
+      ps_f64_item_m<1 | 4, PART>(S, I, J, e0, elo, ehi, E, Rbase, estride, ld, sm);
     else
-      ps_f64_item_m<15, PART>(S, I, J, grp, E, m, Rbase, estride, ld, sm);
+      ps_f64_item_m<15, PART>(S, I, J, e0, elo, ehi, E, Rbase, estride, ld, sm);
   }
 }
 
@@ -225,28 +224,39 @@ template <int PART>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void polesum_f64_kernel(PsLaunch L) {
   __shared__ F64Smem sm;
-  __shared__ int s_item;
-  const int tid = threadIdx.x;
-  int it = -1;
-  if (!L.counter) {
-    const int chunk = (L.n_items + 7) / 8;
-    it = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
-  }
-  for (;;) {
-    if (L.counter) {
-      if (tid == 0) s_item = atomicAdd(L.counter, 1);
-      __syncthreads();
-      it = s_item;
-      __syncthreads();
-    }
-    if (it >= L.n_items) break;
-    const PsItem item = L.items[it];
-    const SymDev &S = L.syms[item.sym];
-    ps_f64_item<PART>(S, item.x, item.y, item.grp, L.E, L.m,
-                L.out.out + L.out.off[item.sym], L.out.estride,
-                L.out.ld_mult * S.n, sm);
-    if (!L.counter) break;
-  }
+  const int chunk = (L.n_items + 7) / 8;
+  const int it = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  if (it >= L.n_items) return;
+  const PsItem item = L.items[it];
+  const SymDev &S = L.syms[item.sym];
+  ps_f64_item<PART>(S, item.x, item.y, item.grp * PS_EG, 0, L.m, L.E,
+                    L.out.out + L.out.off[item.sym], L.out.estride,
+                    L.out.ld_mult * S.n, sm);
+}
+
+// The same over items of 128 energies, for those that the interpolating kernel
+// leaves: a block takes 16 energies of its item.  (Only blocks with energies
+// are launched where that can be told: with idle ones between them the others
+// came two to a CU while CUs stood idle, twice the time on meshes of 64 to
+// 128 energies at 200 channels.)
+template <int PART>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void polesum_f64_rest_kernel(PsLaunch L) {
+  __shared__ F64Smem sm;
+  __shared__ PgDecide dec;
+  constexpr int NB = PG_G / PS_EG;
+  const int total = L.n_items / L.ngrp * L.units, chunk = (total + 7) / 8;
+  const int lin = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  if (lin >= total) return;
+  const int unit = lin % L.units;
+  const PsItem item = L.items[lin / L.units * L.ngrp + unit / NB];
+  const SymDev &S = L.syms[item.sym];
+  const PgGroup P = pg_decide(L, S, item.grp, dec);
+  const int e0 = P.g0 + PS_EG * (unit % NB);
+  if (P.interp || e0 >= P.s1 || e0 + PS_EG <= P.s0) return;
+  ps_f64_item<PART>(S, item.x, item.y, e0, P.s0, P.s1, L.E,
+                    L.out.out + L.out.off[item.sym], L.out.estride,
+                    L.out.ld_mult * S.n, sm);
 }
 
 hipError_t launch_polesum_mixed(const PsLaunch &L, int variant, hipStream_t st);
@@ -259,13 +269,27 @@ int ps_energy_group(int variant) {
     case PS_MX_J16_E4: return 4;
     case PS_PD: return 128;
     case PS_PD64: return 64;
+    case PS_F64_GROUP: return 128;
   }
   return 1;
 }
 
+int ps_groups(int variant, int64_t m, bool aligned) {
+  const int eg = ps_energy_group(variant);
+  if (variant == PS_F64_GROUP && !aligned && m > 0)
+    return (int)((m - 1 + eg - 1) / eg) + 1;
+  return (int)((m + eg - 1) / eg);
+}
+
+int ps_units(int variant, int64_t m, bool aligned) {
+  if (variant != PS_F64_GROUP) return 0;
+  return aligned ? (int)((m + PS_EG - 1) / PS_EG)
+                 : ps_groups(variant, m, false) * (PG_G / PS_EG);
+}
+
 void ps_tiles(const Sym &s, int variant, std::vector<std::pair<int, int>> &out) {
   out.clear();
-  if (variant == PS_F64_T32_E16) {
+  if (variant == PS_F64_T32_E16 || variant == PS_F64_GROUP) {
     const int nt = s.n_pad / PS_T;
     for (int I = 0; I < nt; ++I)
       for (int J = I; J < nt; ++J) out.push_back({I, J});
@@ -285,18 +309,22 @@ hipError_t launch_polesum(const PsLaunch &L, int variant, hipStream_t st) {
   if (L.n_items <= 0 || L.m <= 0) return hipSuccess;
   if (variant == PS_PD) return launch_polesum_pd(L, st);
   if (variant == PS_PD64) return launch_polesum_pd64(L, st);
-  if (variant != PS_F64_T32_E16) return launch_polesum_mixed(L, variant, st);
-  unsigned grid;
-  if (L.counter)
-    grid = (unsigned)std::max(1, std::min(L.grid, L.n_items));
-  else
-    grid = (unsigned)(8 * ((L.n_items + 7) / 8));
-  if (L.part == 1)
-    hipLaunchKernelGGL(polesum_f64_kernel<1>, dim3(grid), dim3(256), 0, st, L);
-  else if (L.part == 2)
-    hipLaunchKernelGGL(polesum_f64_kernel<2>, dim3(grid), dim3(256), 0, st, L);
-  else
-    hipLaunchKernelGGL(polesum_f64_kernel<0>, dim3(grid), dim3(256), 0, st, L);
+  if (variant != PS_F64_T32_E16 && variant != PS_F64_GROUP)
+    return launch_polesum_mixed(L, variant, st);
+  const auto kernel = [&](auto k0, auto k1, auto k2, int blocks) {
+    hipLaunchKernelGGL(L.part == 1 ? k1 : L.part == 2 ? k2 : k0,
+                       dim3((unsigned)blocks), dim3(256), 0, st, L);
+  };
+  if (variant == PS_F64_GROUP) {
+    const hipError_t e = launch_polesum_group(L, st);
+    if (e != hipSuccess) return e;
+    kernel(polesum_f64_rest_kernel<0>, polesum_f64_rest_kernel<1>,
+           polesum_f64_rest_kernel<2>,
+           8 * ((L.n_items / L.ngrp * L.units + 7) / 8));
+  } else {
+    kernel(polesum_f64_kernel<0>, polesum_f64_kernel<1>, polesum_f64_kernel<2>,
+           8 * ((L.n_items + 7) / 8));
+  }
   return hipGetLastError();
 }
 

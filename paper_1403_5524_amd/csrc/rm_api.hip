@@ -417,6 +417,10 @@ struct Plan {
   double *sigma = nullptr;
   double e0 = 0.0;
   std::vector<int64_t> h_work_off;  // host copy of the workspace offsets
+  // chunks begin at multiples of the pole sum's energy groups
+  bool aligned() const {
+    return n_chunks <= 1 || C % ps_energy_group(PS_F64_GROUP) == 0;
+  }
   bool propagate = false;           // some symmetry has outer sectors
   // damped photoionization: per-symmetry offsets of R_re and R_im
   bool damped = false;
@@ -626,13 +630,13 @@ static int tune_variants(const Sym &s, int prec, double delta, double band,
   if (err == hipSuccess) err = hipEventCreate(&b);
   if (err == hipSuccess) err = hipEventCreate(&e);
   for (size_t ci = 0; ci < cands.size() && err == hipSuccess; ++ci) {
-    const int v = cands[ci];
+    const int v = ps_f64_variant(cands[ci], s.nh, mt);
     std::vector<std::pair<int, int>> tiles;
     ps_tiles(s, v, tiles);
-    const int eg = ps_energy_group(v);
+    const int ngrp = ps_groups(v, mt, true);
     std::vector<PsItem> items;
     for (auto &t : tiles)
-      for (int g = 0; g < (mt + eg - 1) / eg; ++g) items.push_back({0, t.first, t.second, g});
+      for (int g = 0; g < ngrp; ++g) items.push_back({0, t.first, t.second, g});
     if (ditems) (void)hipFree(ditems);
     ditems = nullptr;
     err = hipMalloc(&ditems, items.size() * sizeof(PsItem));
@@ -644,6 +648,9 @@ static int tune_variants(const Sym &s, int prec, double delta, double band,
     L.n_items = (int)items.size();
     L.E = E;
     L.m = (int)mt;
+    L.m_all = mt;
+    L.ngrp = ngrp;
+    L.units = ps_units(v, mt, true);
     L.out = PsOut{R, nn, doff, 1};
     L.prec = prec;
     L.delta = delta;
@@ -660,7 +667,7 @@ static int tune_variants(const Sym &s, int prec, double delta, double band,
     }
     if (err == hipSuccess && ms_min < best_ms) {
       best_ms = ms_min;
-      best = v;
+      best = cands[ci];
     }
   }
   if (ditems) (void)hipFree(ditems);
@@ -728,8 +735,7 @@ static int pick_variant(Sym &s, const rm_opts &o, const double *E, int64_t M,
 static void build_items(const Plan &p, int variant, int64_t m,
                         std::vector<PsItem> &out) {
   out.clear();
-  const int eg = ps_energy_group(variant);
-  const int ngrp = (int)((m + eg - 1) / eg);
+  const int ngrp = ps_groups(variant, m, p.aligned());
   std::vector<std::pair<int, int>> tiles;
   for (size_t q = 0; q < p.syms.size(); ++q) {
     if (p.variant[q] != variant) continue;
@@ -819,6 +825,8 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
     int rc = pick_variant(*const_cast<Sym *>(v[q]), o, E, M, st, &p.variant[q]);
     if (rc) return rc;
   }
+  for (size_t q = 0; q < v.size(); ++q)
+    p.variant[q] = ps_f64_variant(p.variant[q], v[q]->nh, M);
   std::vector<SymDev> sd;
   std::vector<int64_t> woff, coff;
   int64_t wacc = 0, cacc = 0;
@@ -1017,6 +1025,10 @@ static int plan_enqueue(Plan &p, hipStream_t st) {
         L.counter = nullptr;
         L.E = p.E + c0;
         L.m = (int)m;
+        L.e_off = c0;
+        L.m_all = p.M;
+        L.ngrp = ps_groups(set.variant, m, p.aligned());
+        L.units = ps_units(set.variant, m, p.aligned());
         L.out = PsOut{p.work, p.work_estride, p.d_work_off, 2};
         L.prec = p.o.prec;
         L.delta = p.o.near_delta;
@@ -1807,6 +1819,10 @@ int rm_rmatrix(rm_sym_t sym, const double *E, int64_t m, const rm_opts *opts,
         L.n_items = set.n_items[t];
         L.E = E + c0;
         L.m = (int)mc;
+        L.e_off = c0;
+        L.m_all = m;
+        L.ngrp = ps_groups(set.variant, mc, p.aligned());
+        L.units = ps_units(set.variant, mc, p.aligned());
         L.out = PsOut{p.work, p.work_estride, p.d_work_off, 2};
         L.prec = p.o.prec;
         L.delta = p.o.near_delta;
@@ -1915,7 +1931,8 @@ int rm_plan_info(rm_plan_t plan, int64_t *chunk, int32_t *n_chunks,
   if (n_chunks) *n_chunks = plan->n_chunks;
   if (variants)
     for (int q = 0; q < n_variants && q < (int)plan->variant.size(); ++q)
-      variants[q] = plan->variant[q];
+      variants[q] = plan->variant[q] == PS_F64_GROUP ? PS_F64_T32_E16
+                                                     : plan->variant[q];
   return RM_OK;
 }
 

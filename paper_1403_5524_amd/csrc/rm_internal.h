@@ -170,7 +170,8 @@ enum PsVariant {
   PS_MX_J8_E8 = 2,      // mixed, 8 column blocks, 8 energies per WG
   PS_MX_J16_E4 = 3,     // mixed, 16 column blocks, 4 energies per WG
   PS_PD = 4,            // mixed, pair-major GEMM over precomputed w_ik w_jk
-  PS_PD64 = 5           // FP64, pair-major GEMM
+  PS_PD64 = 5,          // FP64, pair-major GEMM
+  PS_F64_GROUP = 6      // FP64, far poles interpolated over 128 energies
 };
 constexpr int kPairBlock = 256;   // pairs per pair-major workgroup tile
 
@@ -194,6 +195,8 @@ struct PsLaunch {
   int grid;             // persistent grid size (used with counter)
   const double *E;
   int m;
+  int64_t e_off, m_all; // E[-e_off .. m_all - e_off) is the whole mesh
+  int ngrp, units;      // PS_F64_GROUP: groups, and sixteens of energies, a tile
   PsOut out;
   int prec;
   double delta;         // near tier: FP64 operands
@@ -205,10 +208,30 @@ struct PsLaunch {
 hipError_t launch_polesum(const PsLaunch &L, int variant, hipStream_t st);
 hipError_t launch_polesum_pd(const PsLaunch &L, hipStream_t st);
 hipError_t launch_polesum_pd64(const PsLaunch &L, hipStream_t st);
+hipError_t launch_polesum_group(const PsLaunch &L, hipStream_t st);
+// The FP64 scaled-W sum of nh poles on a mesh of m energies: in groups from
+// 64 energies and 512 poles on.  Far poles then cost 16 energies' work per
+// group (200 channels, 8000 poles, mesh step 1e-4: 0.40 ms at 64 energies
+// against 1.17); fewer energies than that leave too little to save, and with
+// few poles the decision and the interpolation weights are most of the time
+// (5 channels, 64 poles: 22 us against 6.8; 33 channels, 1000 poles: 73 us
+// against 114).
+constexpr int kPsGroupMin = 64, kPsGroupPoles = 512;
+inline int ps_f64_variant(int variant, int nh, int64_t m) {
+  return variant == PS_F64_T32_E16 && m >= kPsGroupMin && nh >= kPsGroupPoles
+             ? PS_F64_GROUP
+             : variant;
+}
 hipError_t launch_pd64_build(const Sym &s, hipStream_t st);
 // Form the pair products of s for prec (FP32 or BF16X3) into its planes.
 hipError_t launch_pd_build(const Sym &s, int prec, hipStream_t st);
 int ps_energy_group(int variant);         // energies per work item
+// Energy groups of a chunk of m energies, and (PS_F64_GROUP) how many blocks
+// of 16 energies they make.  Groups of that variant are cut on the whole mesh:
+// unless chunks begin at multiples of a group (`aligned`) one may begin and
+// end inside a group.
+int ps_groups(int variant, int64_t m, bool aligned);
+int ps_units(int variant, int64_t m, bool aligned);
 // Tile items of one symmetry for a variant: (x, y) pairs, in order.
 void ps_tiles(const Sym &s, int variant, std::vector<std::pair<int, int>> &out);
 
