@@ -273,6 +273,82 @@ static int check_opts(const rm_opts *o, rm_opts *out, bool photo = false) {
   return RM_OK;
 }
 
+// Stream-ordered memory of a call (workspaces, tables).  It comes from a pool
+// of this library's own, one per device, that keeps up to kPoolKeep bytes
+// between calls: the device's default pool gives everything back at the next
+// synchronisation, and mapping it again took longer than the kernels of an
+// ordinary call (K matrices of 60 channels 14.5 ms, 3.4 of them kernels).
+// The pool's idle memory is given back when the last symmetry handle of the
+// device is freed, and before an allocation of this library is given up.
+// Blocks are handed from stream to stream by the runtime, in stream order.
+constexpr uint64_t kPoolKeep = 16ull << 30;
+struct DevicePool {
+  hipMemPool_t pool = nullptr;
+  int handles = 0;
+};
+static std::mutex g_pool_mu;
+static std::map<int, DevicePool> g_pools;
+
+static hipError_t device_pool(hipMemPool_t *out) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  DevicePool &d = g_pools[dev];
+  if (!d.pool) {
+    hipMemPoolProps props{};
+    props.allocType = hipMemAllocationTypePinned;
+    props.handleTypes = hipMemHandleTypeNone;
+    props.location.type = hipMemLocationTypeDevice;
+    props.location.id = dev;
+    e = hipMemPoolCreate(&d.pool, &props);
+    uint64_t keep = kPoolKeep;
+    if (e == hipSuccess)
+      e = hipMemPoolSetAttribute(d.pool, hipMemPoolAttrReleaseThreshold, &keep);
+    if (e != hipSuccess) return e;
+  }
+  *out = d.pool;
+  return hipSuccess;
+}
+
+// Give the pool's idle memory back (st: a stream whose frees may be pending).
+static void pool_trim(hipStream_t st) {
+  hipMemPool_t pool;
+  if (hipStreamSynchronize(st) != hipSuccess) return;
+  if (device_pool(&pool) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+}
+
+static hipError_t pool_alloc(void **p, size_t bytes, hipStream_t st) {
+  hipMemPool_t pool;
+  hipError_t e = device_pool(&pool);
+  if (e == hipSuccess) e = hipMallocFromPoolAsync(p, bytes, pool, st);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    pool_trim(st);
+    e = hipMallocFromPoolAsync(p, bytes, pool, st);
+  }
+  return e;
+}
+
+// hipMalloc that does not fail for what the pool holds.
+static hipError_t device_malloc(void **p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    pool_trim(nullptr);
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
+// A symmetry handle of device `dev` appears (+1) or goes (-1).
+static void pool_handle(int dev, int change) {
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  DevicePool &d = g_pools[dev];
+  d.handles += change;
+  if (d.handles == 0 && d.pool) (void)hipMemPoolTrimTo(d.pool, 0);
+}
+
 struct DevBuf {
   void *p = nullptr;
   hipStream_t st = nullptr;
@@ -284,7 +360,7 @@ struct DevBuf {
 static int dev_alloc(DevBuf &b, size_t bytes, hipStream_t st) {
   b.st = st;
   if (bytes == 0) bytes = 8;
-  hipError_t e = hipMallocAsync(&b.p, bytes, st);
+  hipError_t e = pool_alloc(&b.p, bytes, st);
   if (e != hipSuccess) {
     b.p = nullptr;
     return fail(e == hipErrorOutOfMemory ? RM_ERR_NOMEM : RM_ERR_HIP,
@@ -402,7 +478,8 @@ struct Plan {
   ChanSlot *chan = nullptr;
   int *counters = nullptr;         // one per chunk (match kernel)
   int match_grid = 0;
-  bool owns_async = false;         // workspace from hipMallocAsync
+  void *block = nullptr;           // all of the above and the tables
+  bool owns_async = false;         // ... from the pool
   bool in_arena = false;           // tables and workspace in an Arena
   hipStream_t alloc_stream = nullptr;
   // graph
@@ -450,27 +527,19 @@ static void plan_free_device(Plan &p) {
     p.counters = nullptr;
     return;
   }
-  for (auto &set : p.sets)
-    for (int t = 0; t < 2; ++t)
-      if (set.d_items[t]) (void)hipFree(set.d_items[t]);
   p.sets.clear();
-  void *tabs[] = {p.d_syms, p.d_work_off, p.d_chan_off, p.d_rre_off,
-                  p.d_rim_off};
-  for (void *q : tabs)
-    if (q) (void)hipFree(q);
   p.d_syms = nullptr;
   p.d_work_off = p.d_chan_off = nullptr;
   p.d_rre_off = p.d_rim_off = nullptr;
-  p.ext = nullptr;  // part of p.work
+  p.ext = nullptr;
   p.ext_flags = nullptr;
-  void *ws[] = {p.work, p.chan, p.counters};
-  for (void *q : ws) {
-    if (!q) continue;
+  if (p.block) {
     if (p.owns_async)
-      (void)hipFreeAsync(q, p.alloc_stream);
+      (void)hipFreeAsync(p.block, p.alloc_stream);
     else
-      (void)hipFree(q);
+      (void)hipFree(p.block);
   }
+  p.block = nullptr;
   p.work = nullptr;
   p.chan = nullptr;
   p.counters = nullptr;
@@ -557,12 +626,12 @@ static bool ensure_pd(Sym &s, int prec, hipStream_t st) {
   const size_t half = (size_t)s.np_pad * s.nh_pad * sizeof(uint16_t);
   hipError_t e;
   if (bf) {
-    e = hipMalloc((void **)&s.Ph, half);
-    if (e == hipSuccess) e = hipMalloc((void **)&s.Pl, half);
+    e = device_malloc((void **)&s.Ph, half);
+    if (e == hipSuccess) e = device_malloc((void **)&s.Pl, half);
   } else if (f64) {
-    e = hipMalloc((void **)&s.P64, 4 * half);
+    e = device_malloc((void **)&s.P64, 4 * half);
   } else {
-    e = hipMalloc((void **)&s.P32, 2 * half);
+    e = device_malloc((void **)&s.P32, 2 * half);
   }
   if (e == hipSuccess) e = f64 ? launch_pd64_build(s, st) : launch_pd_build(s, prec, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -620,9 +689,9 @@ static int tune_variants(const Sym &s, int prec, double delta, double band,
   hipEvent_t b = nullptr, e = nullptr;
   int best = cands[0];
   float best_ms = 1e30f;
-  hipError_t err = hipMalloc(&R, (size_t)(mt * nn) * sizeof(double));
-  if (err == hipSuccess) err = hipMalloc(&dsym, sizeof(SymDev));
-  if (err == hipSuccess) err = hipMalloc(&doff, sizeof(int64_t));
+  hipError_t err = device_malloc((void **)&R, (size_t)(mt * nn) * sizeof(double));
+  if (err == hipSuccess) err = device_malloc((void **)&dsym, sizeof(SymDev));
+  if (err == hipSuccess) err = device_malloc((void **)&doff, sizeof(int64_t));
   const SymDev sd = s.dev();
   const int64_t zero = 0;
   if (err == hipSuccess) err = hipMemcpy(dsym, &sd, sizeof sd, hipMemcpyHostToDevice);
@@ -639,7 +708,7 @@ static int tune_variants(const Sym &s, int prec, double delta, double band,
       for (int g = 0; g < ngrp; ++g) items.push_back({0, t.first, t.second, g});
     if (ditems) (void)hipFree(ditems);
     ditems = nullptr;
-    err = hipMalloc(&ditems, items.size() * sizeof(PsItem));
+    err = device_malloc((void **)&ditems, items.size() * sizeof(PsItem));
     if (err == hipSuccess)
       err = hipMemcpy(ditems, items.data(), items.size() * sizeof(PsItem), hipMemcpyHostToDevice);
     PsLaunch L{};
@@ -798,7 +867,7 @@ static int pick_variant_noalloc(const Sym &s, const rm_opts &o) {
 static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
                       const double *E, int64_t M, const rm_opts &o,
                       hipStream_t st, bool async, double ws_budget,
-                      Arena *arena = nullptr) {
+                      Arena *arena = nullptr, bool grow = false) {
   p.o = o;
   p.n_target = n_target;
   p.M = M;
@@ -900,6 +969,9 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
     // complex route cost about three ordinary ones, and with only two
     // energies per wavefront a chunk would end with whichever of them came
     // last (24 % more matching time at 4096, 3 % at 16384)
+    const double most = (double)std::min<int64_t>(M, p.want_t ? 16384 : 4096);
+    if (grow && o.chunk <= 0 && ws_budget < most * (per_energy + 64.0))
+      ws_budget = workspace_budget(ws_budget);
     C = o.chunk > 0 ? o.chunk : (int64_t)(ws_budget / (per_energy + 64.0));
     C = std::max<int64_t>(1, std::min<int64_t>(C, p.want_t ? 16384 : 4096));
     if (o.chunk <= 0) C = std::max<int64_t>(std::min<int64_t>(64, M), C);
@@ -910,53 +982,52 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
   p.tail = M - (int64_t)(p.n_chunks - 1) * C;
   p.in_arena = arena != nullptr;
   hipError_t e = hipSuccess;
-  // device memory for a table: from the arena or hipMalloc
-  auto get = [&](void **ptr, size_t bytes) -> hipError_t {
-    if (!arena) return hipMalloc(ptr, bytes);
-    return arena->take(ptr, bytes) ? hipSuccess : hipErrorOutOfMemory;
+  // a table: from the arena with a copy of its own, else a piece of one
+  // allocation with the workspace and of one copy
+  std::vector<char> blob;
+  std::vector<std::pair<void **, size_t>> pieces;
+  auto table = [&](void **ptr, const void *src, size_t bytes) {
+    if (e != hipSuccess) return;
+    if (arena) {
+      e = arena->take(ptr, bytes) ? hipSuccess : hipErrorOutOfMemory;
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(*ptr, src, bytes, hipMemcpyHostToDevice, st);
+      return;
+    }
+    const size_t at = (blob.size() + 255) & ~(size_t)255;
+    blob.resize(at + bytes);
+    std::memcpy(blob.data() + at, src, bytes);
+    pieces.push_back({ptr, at});
   };
-  auto put = [&](void *dst, const void *src, size_t bytes) -> hipError_t {
-    return arena ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st)
-                 : hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
-  };
-  e = get((void **)&p.d_syms, sd.size() * sizeof(SymDev));
-  if (e == hipSuccess) e = get((void **)&p.d_work_off, woff.size() * sizeof(int64_t));
-  if (e == hipSuccess) e = get((void **)&p.d_chan_off, coff.size() * sizeof(int64_t));
-  if (e == hipSuccess) e = put(p.d_syms, sd.data(), sd.size() * sizeof(SymDev));
-  if (e == hipSuccess) e = put(p.d_work_off, woff.data(), woff.size() * sizeof(int64_t));
-  if (e == hipSuccess) e = put(p.d_chan_off, coff.data(), coff.size() * sizeof(int64_t));
+  table((void **)&p.d_syms, sd.data(), sd.size() * sizeof(SymDev));
+  table((void **)&p.d_work_off, woff.data(), woff.size() * sizeof(int64_t));
+  table((void **)&p.d_chan_off, coff.data(), coff.size() * sizeof(int64_t));
   if (p.damped && !arena) {
     std::vector<int64_t> re(v.size()), im(v.size());
     for (size_t q = 0; q < v.size(); ++q) {
       re[q] = woff[q] + sys_doubles_damped(v[q]->n);
       im[q] = re[q] + (int64_t)v[q]->n * v[q]->n;
     }
-    if (e == hipSuccess) e = get((void **)&p.d_rre_off, re.size() * sizeof(int64_t));
-    if (e == hipSuccess) e = get((void **)&p.d_rim_off, im.size() * sizeof(int64_t));
-    if (e == hipSuccess) e = put(p.d_rre_off, re.data(), re.size() * sizeof(int64_t));
-    if (e == hipSuccess) e = put(p.d_rim_off, im.data(), im.size() * sizeof(int64_t));
+    table((void **)&p.d_rre_off, re.data(), re.size() * sizeof(int64_t));
+    table((void **)&p.d_rim_off, im.data(), im.size() * sizeof(int64_t));
   }
   std::vector<int> vars(p.variant.begin(), p.variant.end());
   std::sort(vars.begin(), vars.end());
   vars.erase(std::unique(vars.begin(), vars.end()), vars.end());
   std::vector<std::vector<PsItem>> staged;  // host tables alive until synced
-  for (int var : vars) {
-    if (e != hipSuccess) break;
-    Plan::ItemSet set;
-    set.variant = var;
+  p.sets.resize(vars.size());
+  for (size_t k = 0; k < vars.size(); ++k) {
+    Plan::ItemSet &set = p.sets[k];
+    set.variant = vars[k];
     for (int t = 0; t < 2; ++t) {
       const int64_t m = (t == 0) ? C : p.tail;
       staged.emplace_back();
       std::vector<PsItem> &items = staged.back();
-      build_items(p, var, m, items);
+      build_items(p, vars[k], m, items);
       set.n_items[t] = (int)items.size();
-      if (items.empty()) continue;
-      e = get((void **)&set.d_items[t], items.size() * sizeof(PsItem));
-      if (e == hipSuccess)
-        e = put(set.d_items[t], items.data(), items.size() * sizeof(PsItem));
-      if (e != hipSuccess) break;
+      if (!items.empty())
+        table((void **)&set.d_items[t], items.data(), items.size() * sizeof(PsItem));
     }
-    p.sets.push_back(set);
   }
   // the host tables go out of scope here: wait for their copies
   if (arena && e == hipSuccess) e = hipStreamSynchronize(st);
@@ -983,14 +1054,23 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
     if (e != hipSuccess)
       return fail(RM_ERR_ARG, "workspace of %zu bytes does not fit the "
                   "%zu-byte scratch", wbytes + xbytes + cbytes, arena->cap);
-  } else if (async) {
-    e = hipMallocAsync((void **)&p.work, wbytes + xbytes, st);
-    if (e == hipSuccess) e = hipMallocAsync((void **)&p.chan, cbytes, st);
-    if (e == hipSuccess) e = hipMallocAsync((void **)&p.counters, kbytes, st);
   } else {
-    e = hipMalloc((void **)&p.work, wbytes + xbytes);
-    if (e == hipSuccess) e = hipMalloc((void **)&p.chan, cbytes);
-    if (e == hipSuccess) e = hipMalloc((void **)&p.counters, kbytes);
+    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const size_t at_chan = up(wbytes + xbytes), at_cnt = at_chan + up(cbytes);
+    const size_t at_tab = at_cnt + up(kbytes);
+    e = async ? pool_alloc(&p.block, at_tab + blob.size(), st)
+              : device_malloc(&p.block, at_tab + blob.size());
+    if (e == hipSuccess) {
+      char *base = (char *)p.block;
+      p.work = (double *)base;
+      p.chan = (ChanSlot *)(base + at_chan);
+      p.counters = (int *)(base + at_cnt);
+      for (auto &x : pieces) *x.first = base + at_tab + x.second;
+      e = hipMemcpyAsync(base + at_tab, blob.data(), blob.size(),
+                         hipMemcpyHostToDevice, st);
+      // the host side goes out of scope
+      if (e == hipSuccess) e = hipStreamSynchronize(st);
+    }
   }
   if (e == hipSuccess && p.ext_slots) {
     p.ext = p.work + C * wacc;
@@ -1141,6 +1221,7 @@ static int free_sym(Sym *s) {
     if (p) (void)hipFree(p);
   delete[] s->h_e_thr;
   delete[] s->h_perm;
+  pool_handle(s->device, -1);
   delete s;
   return RM_OK;
 }
@@ -1212,10 +1293,11 @@ int rm_load_poles(const rm_poles_desc *d, rm_sym_t *out, void *stream) {
   std::memset((void *)s, 0, sizeof(Sym));
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) {
-    free_sym(s);
+    delete s;
     return fail(RM_ERR_HIP, "hipGetDevice failed");
   }
   s->device = dev;
+  pool_handle(dev, 1);
   s->n = n;
   s->nh = nh;
   s->n_pad = (n + kChanPad - 1) / kChanPad * kChanPad;
@@ -1293,7 +1375,7 @@ int rm_load_poles(const rm_poles_desc *d, rm_sym_t *out, void *stream) {
 
   hipError_t e = hipSuccess;
 #define RM_ALLOC_COPY(dst, src, bytes)                                        \
-  if (e == hipSuccess) e = hipMalloc((void **)&(dst), (bytes));              \
+  if (e == hipSuccess) e = device_malloc((void **)&(dst), (bytes));              \
   if (e == hipSuccess)                                                       \
     e = hipMemcpyAsync((dst), (src), (bytes), hipMemcpyHostToDevice, st);
   RM_ALLOC_COPY(s->E_pole, Ep.data(), hpad * sizeof(double));
@@ -1359,7 +1441,7 @@ int rm_sweep_energies(const rm_sym_t *syms, int32_t n_sym, int32_t n_target,
   hipStream_t st = (hipStream_t)stream;
   Plan p;
   rc = plan_build(p, syms, n_sym, n_target, E, M, o, st, true,
-                  workspace_budget(16.0e9));
+                  16.0e9, nullptr, true);
   if (!rc) {
     p.E = E;
     p.omega = omega;
@@ -1559,8 +1641,8 @@ int rm_set_propagation(rm_sym_t sym, double A, int32_t n_sec, int32_t lmax,
   for (int i = 0; i < n; ++i)
     for (int j = 0; j < n; ++j) O[(size_t)n_sec * nsq + (size_t)i * n + j] = U[(size_t)j * n + i];
   double *dO = nullptr, *de = nullptr;
-  hipError_t e = hipMalloc((void **)&dO, O.size() * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc((void **)&de, eps.size() * sizeof(double));
+  hipError_t e = device_malloc((void **)&dO, O.size() * sizeof(double));
+  if (e == hipSuccess) e = device_malloc((void **)&de, eps.size() * sizeof(double));
   if (e == hipSuccess) e = hipMemcpy(dO, O.data(), O.size() * sizeof(double), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(de, eps.data(), eps.size() * sizeof(double), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
@@ -1581,7 +1663,7 @@ int rm_set_propagation(rm_sym_t sym, double A, int32_t n_sec, int32_t lmax,
           Bc[((size_t)i * lmax + lam) * n + m] =
               beta[((int64_t)lam * n + sym->h_perm[i]) * n + sym->h_perm[m]] * sc;
       }
-    e = hipMalloc((void **)&dB, Bc.size() * sizeof(double));
+    e = device_malloc((void **)&dB, Bc.size() * sizeof(double));
     if (e == hipSuccess)
       e = hipMemcpy(dB, Bc.data(), Bc.size() * sizeof(double), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
@@ -1631,7 +1713,7 @@ int rm_load_dipoles(rm_sym_t sym, const double *d, void *stream) {
   hipStream_t st = (hipStream_t)stream;
   // kernels already queued may still read the old vector
   RM_HIP(hipStreamSynchronize(st));
-  if (!sym->dip) RM_HIP(hipMalloc((void **)&sym->dip, h.size() * sizeof(double)));
+  if (!sym->dip) RM_HIP(device_malloc((void **)&sym->dip, h.size() * sizeof(double)));
   RM_HIP(hipMemcpy(sym->dip, h.data(), h.size() * sizeof(double),
                    hipMemcpyHostToDevice));
   return RM_OK;
@@ -1649,7 +1731,7 @@ int rm_load_widths(rm_sym_t sym, const double *gamma, void *stream) {
   }
   hipStream_t st = (hipStream_t)stream;
   RM_HIP(hipStreamSynchronize(st));  // queued kernels may read the old ones
-  if (!sym->gam) RM_HIP(hipMalloc((void **)&sym->gam, h.size() * sizeof(double)));
+  if (!sym->gam) RM_HIP(device_malloc((void **)&sym->gam, h.size() * sizeof(double)));
   RM_HIP(hipMemcpy(sym->gam, h.data(), h.size() * sizeof(double),
                    hipMemcpyHostToDevice));
   return RM_OK;
@@ -1685,7 +1767,7 @@ int rm_photoionization(const rm_sym_t *syms, int32_t n_sym, const double *E,
   Plan p;
   p.want_t = false;
   rc = plan_build(p, syms, n_sym, n_tgt, E, M, o, st, true,
-                  workspace_budget(16.0e9));
+                  16.0e9, nullptr, true);
   if (!rc) {
     p.E = E;
     p.sigma = sigma;
