@@ -216,7 +216,7 @@ int rm_sweep_energies_noalloc(const rm_sym_t *syms, int32_t n_sym,
  * the symmetries by cost, sizes the chunks and the workspace (owned by the
  * plan), builds the grouped pole-sum work tables (largest symmetries first),
  * and records the whole sweep -- per chunk one grouped pole-sum launch per
- * tile variant and one persistent matching launch covering every symmetry
+ * tile variant and the matching of every symmetry
  * and energy of the chunk -- into a hipGraph bound to E, omega and status.
  * rm_plan_execute replays it on `stream` (the caller may change the contents
  * of E between replays, not the pointers).  Replays of one plan must not

@@ -39,7 +39,7 @@ struct OpenVals {
   int ok;
 };
 
-__device__ inline OpenVals coulomb_open(int L, double z, double k, double a) {
+__device__ __forceinline__ OpenVals coulomb_open(int L, double z, double k, double a) {
   const double eta = -z / k;
   const double rho = k * a;
   const double Lf = (double)L;
@@ -118,7 +118,7 @@ __device__ inline OpenVals coulomb_open(int L, double z, double k, double a) {
 
 // psi(y) for y > 0: upward recurrence to y >= 10, then the asymptotic series
 // ln y - 1/(2y) - sum_n B_2n / (2n y^2n) through B_14.
-__device__ inline double digamma_pos(double y) {
+__device__ __forceinline__ double digamma_pos(double y) {
   double acc = 0.0;
   while (y < 10.0) {
     acc -= 1.0 / y;
@@ -142,12 +142,12 @@ struct ClosedVals {
 
 // Switch between the continued fraction (accurate for small kappa, worse as
 // l grows) and the U series (accurate for small x = 2 z a / kappa).
-__device__ inline double whittaker_kappa_switch(int l) {
+__device__ __forceinline__ double whittaker_kappa_switch(int l) {
   const double v = 36.0 - 6.0 * l;
   return v > 8.0 ? v : 8.0;
 }
 
-__device__ inline ClosedVals whittaker_cf(int l, double kappa, double x) {
+__device__ __forceinline__ ClosedVals whittaker_cf(int l, double kappa, double x) {
   // r = W_{kappa-1}/W_kappa = 1/(b_1 - c_{kappa-1}/(b_2 - c_{kappa-2}/...)),
   // b_j = x + 2j - 2 kappa, c_m = (m - 1/2)^2 - mu^2; convergence counted
   // only once j is past kappa + mu.
@@ -190,7 +190,7 @@ __device__ inline ClosedVals whittaker_cf(int l, double kappa, double x) {
   return out;
 }
 
-__device__ inline ClosedVals whittaker_useries(int l, double kappa, double x) {
+__device__ __forceinline__ ClosedVals whittaker_useries(int l, double kappa, double x) {
   const int n = 2 * l + 1;
   const double a = l + 1.0 - kappa;
   const double N = rint(kappa);
@@ -270,7 +270,7 @@ __device__ inline ClosedVals whittaker_useries(int l, double kappa, double x) {
   return out;
 }
 
-__device__ inline ClosedVals whittaker_closed(int l, double z, double phi,
+__device__ __forceinline__ ClosedVals whittaker_closed(int l, double z, double phi,
                                               double a) {
   const double kappa = z / phi;
   const double x = 2.0 * phi * a;

@@ -1,9 +1,8 @@
 // Outer-region propagation kernel.  It has a translation unit of its own so
-// that the wavefront linear algebra it shares with the matching kernel (LU,
-// GEMM) is compiled separately for each kernel: sharing those routines in
-// one unit changed the matching kernel's register allocation.
-#define RM_MATCH_DEVICE_ONLY
-#include "match.hip"
+// that the team linear algebra it shares with the matching kernel (LU, GEMM)
+// is compiled separately for each kernel: sharing those routines in one unit
+// changed the matching kernel's register allocation.
+#include "match_core.h"
 
 namespace rmx {
 
@@ -16,34 +15,38 @@ namespace rmx {
 // exact for a constant potential; finally X <- O^T X O back to the channel
 // basis and R(A) = X / A replaces R(a) in Aug's left half.  The step is one
 // linear solve, (c - kappa^2 s X)^T Y = (c X + s)^T, Y = X_new^T, set up in
-// Aug = [D^T | N^T] for the wavefront LU; X itself lives in Kb.  The
+// Aug = [D^T | N^T] for the team's LU; X itself lives in Kb.  The
 // per-channel c, s, kappa^2 s of a sector go to the channel slots, which
 // the channel functions fill only afterwards.  Returns nonzero if a sector
 // system was singular.
-__device__ int wave_propagate(const SymDev &S, double Ee, double *Aug, int ld,
-                              double *Kb, ChanSlot *ch, WaveLds &W) {
-  const int lane = lane_id();
+template <int NW, int NAMAX>
+__device__ __forceinline__ int team_propagate(const SymDev &S, double Ee, RM_G double *Aug, int ld,
+                              RM_G double *Kb, RM_G ChanSlot *ch, RM_L TeamLds<NW> &W) {
+  ld = uni(ld);
+  const int tid = team_tid<NW>();
   const int n = S.n;
   const int nsq = n * n;
   int flag = 0;
   // X = a R(a) in Aug's left half
-  for (int q = lane; q < nsq; q += WT) Aug[(int64_t)(q / n) * ld + q % n] *= S.a;
-  wave_sync();
+  team_each<NW>(
+      n, n, [&](int i, int j) { return Aug[(int64_t)i * ld + j]; },
+      [&](int i, int j, double v) { Aug[(int64_t)i * ld + j] = v * S.a; });
+  team_sync<NW>();
   for (int t = 0; t <= S.n_sec; ++t) {
-    const double *O = S.prop_O + (int64_t)t * nsq;
+    const RM_G double *O = as_g(S.prop_O + (int64_t)t * nsq);
     // Kb = O^T (X O).  X is symmetric, so inside the sectors only the tiles
     // that meet the product's lower triangle are formed and the assembly
     // below reads element (i, j) at (max, min); the final change of basis
     // forms all of it
-    wave_gemm_wide<2, 0, 2, 4>(Aug + n, ld, Aug, ld, O, n, n, n, n);
+    team_gemm_wide<NW, 2, 0, 2, 4>(Aug + n, ld, Aug, ld, O, n, n, n, n);
     if (t == S.n_sec) {
-      wave_gemm_wide<2, G_TA, 2, 4>(Kb, n, O, n, Aug + n, ld, n, n, n);
+      team_gemm_wide<NW, 2, G_TA, 2, 4>(Kb, n, O, n, Aug + n, ld, n, n, n);
       break;
     }
-    wave_gemm_wide<2, G_TA | G_LOWER, 2, 4>(Kb, n, O, n, Aug + n, ld, n, n, n);
-    const double *eps = S.prop_eps + (int64_t)t * n;
+    team_gemm_wide<NW, 2, G_TA | G_LOWER, 2, 4>(Kb, n, O, n, Aug + n, ld, n, n, n);
+    const RM_G double *eps = as_g(S.prop_eps + (int64_t)t * n);
     const double h = S.h_sec;
-    for (int i = lane; i < n; i += WT) {
+    for (int i = tid; i < n; i += WT * NW) {
       const double k2 = Ee - eps[i];
       const double k = sqrt(fabs(k2));
       double c, sn;
@@ -61,57 +64,35 @@ __device__ int wave_propagate(const SymDev &S, double Ee, double *Aug, int ld,
       ch[i].d2 = sn;
       ch[i].s = k2 * sn;
     }
-    wave_sync();
+    team_sync<NW>();
     // Aug = [(c - kappa^2 s X)^T | (c X + s)^T]
-    for (int q0 = lane; q0 < nsq; q0 += UNR * WT) {
-      double x[UNR], cj[UNR], sj[UNR], ksj[UNR], ci[UNR];
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int q = q0 + u * WT;
-        const bool in = q < nsq;
-        const int i = in ? q / n : 0, j = in ? q % n : 0;
-        const int hi = i > j ? i : j, lo = i + j - hi;
-        x[u] = in ? Kb[(int64_t)hi * n + lo] : 0.0;
-        cj[u] = ch[j].d1;
-        sj[u] = ch[j].d2;
-        ksj[u] = ch[j].s;
-        ci[u] = ch[i].d1;
-      }
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int q = q0 + u * WT;
-        if (q >= nsq) continue;
-        const int i = q / n, j = q % n;
-        Aug[(int64_t)i * ld + j] = (i == j ? ci[u] : 0.0) - ksj[u] * x[u];
-        Aug[(int64_t)i * ld + n + j] = cj[u] * x[u] + (i == j ? sj[u] : 0.0);
-      }
-    }
-    wave_sync();
-    flag |= wave_lu_solve(Aug, n, ld, n, W);
+    team_each<NW>(
+        n, n,
+        [&](int i, int j) { return Kb[(int64_t)max(i, j) * n + min(i, j)]; },
+        [&](int i, int j, double x) {
+          Aug[(int64_t)i * ld + j] = (i == j ? ch[i].d1 : 0.0) - ch[j].s * x;
+          Aug[(int64_t)i * ld + n + j] = ch[j].d1 * x + (i == j ? ch[j].d2 : 0.0);
+        });
+    team_sync<NW>();
+    flag |= team_lu_solve<NW, NAMAX>(Aug, n, ld, n, W);
     // X_new = sym(Y^T) into Aug's left half (reads only the right half)
-    for (int q0 = lane; q0 < nsq; q0 += UNR * WT) {
-      double a[UNR], b[UNR];
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int q = q0 + u * WT;
-        const bool in = q < nsq;
-        const int i = in ? q / n : 0, j = in ? q % n : 0;
-        a[u] = in ? Aug[(int64_t)i * ld + n + j] : 0.0;
-        b[u] = in ? Aug[(int64_t)j * ld + n + i] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int q = q0 + u * WT;
-        if (q < nsq) Aug[(int64_t)(q / n) * ld + q % n] = 0.5 * (a[u] + b[u]);
-      }
-    }
-    wave_sync();
+    team_each<NW>(
+        n, n,
+        [&](int i, int j) {
+          return make_double2(Aug[(int64_t)i * ld + n + j],
+                              Aug[(int64_t)j * ld + n + i]);
+        },
+        [&](int i, int j, double2 y) {
+          Aug[(int64_t)i * ld + j] = 0.5 * (y.x + y.y);
+        });
+    team_sync<NW>();
   }
   // R(A) = X / A into Aug's left half
   const double rA = 1.0 / S.A;
-  for (int q = lane; q < nsq; q += WT)
-    Aug[(int64_t)(q / n) * ld + q % n] = Kb[q] * rA;
-  wave_sync();
+  team_each<NW>(
+      n, n, [&](int i, int j) { return Kb[(int64_t)i * n + j]; },
+      [&](int i, int j, double v) { Aug[(int64_t)i * ld + j] = v * rA; });
+  team_sync<NW>();
   return flag;
 }
 
@@ -160,37 +141,39 @@ __device__ inline int gl_pos(int p, int Q) { return ((-p) % Q + Q) % Q; }
 // The matching system at A with the expansion's solutions, in place of the
 // one the matching kernel assembles from Coulomb functions: R(A) in Aug's
 // left half on entry (copied to Kb), closed channels' functions in ch, the
-// open channels j < no in blocks of kGlCols columns (lane l serves column
-// l mod kGlCols of a block).  Per block and order one wavefront GEMM forms
+// open channels j < no in blocks of kGlCols columns (thread t serves column
+// t mod kGlCols of a block).  Per block and order one team GEMM forms
 // V(p) from the stacked couplings and the doubled ring of earlier orders;
 // at the end [A C' | A S'] is multiplied by R for
 //   Aug = [C - R A C' | diag(d1_Q) - R_Q diag(d2_Q) | R A S' - S].
 // gw: gl_doubles(n, lmax) doubles of scratch.  Returns RM_E_ASYM_NOCONV if
 // some channel's first omitted term exceeds kGlFlag.
-__device__ int wave_gailitis_system(const SymDev &S, double Ee, double *Aug,
-                                    int ld, double *Kb, const ChanSlot *ch,
-                                    int no, double *gw) {
-  const int lane = lane_id();
+template <int NW>
+__device__ __forceinline__ int team_gailitis_system(const SymDev &S, double Ee, RM_G double *Aug,
+                                    int ld, RM_G double *Kb, const RM_G ChanSlot *ch,
+                                    int no, RM_G double *gw, RM_L TeamLds<NW> &W) {
+  ld = uni(ld); no = uni(no);
+  const int tid = team_tid<NW>();
   const int n = S.n, nc = n - no;
   const double r = S.A, ir = 1.0 / S.A;
   const int Q = gl_ring(S.lmax);
   constexpr int CB = kGlCols, CW = 2 * kGlCols;
   const int64_t slot = (int64_t)n * CW;
-  double *ring = gw;
-  double *Vs = ring + 2 * Q * slot;
-  double *g = Vs + 2 * slot;
-  double *gp = g + slot;
-  double *Y = gp + slot;
-  double *X = Y + slot;
+  RM_G double *ring = gw;
+  RM_G double *Vs = ring + 2 * Q * slot;
+  RM_G double *g = Vs + 2 * slot;
+  RM_G double *gp = g + slot;
+  RM_G double *Y = gp + slot;
+  RM_G double *X = Y + slot;
   int bits = 0;
-  wave_copy(Kb, n, Aug, ld, n, n);
-  wave_sync();
-  for (int q = lane; q < n * nc; q += WT) {
+  team_copy<NW>(Kb, n, Aug, ld, n, n);
+  team_sync<NW>();
+  for (int q = tid; q < n * nc; q += WT * NW) {
     const int i = q / nc, j = no + q % nc;
     Aug[(int64_t)i * ld + j] =
         (i == j ? ch[j].d1 : 0.0) - Kb[(int64_t)i * n + j] * ch[j].d2;
   }
-  const int jj = lane & (CB - 1);
+  const int jj = tid & (CB - 1);
   for (int j0 = 0; j0 < no; j0 += CB) {
     const int j = j0 + jj;
     const bool real_col = j < no;
@@ -198,36 +181,36 @@ __device__ int wave_gailitis_system(const SymDev &S, double Ee, double *Aug,
     const double ej = S.e_thr[jc];
     const double kj = real_col ? sqrt(Ee - ej) : 1.0;
     const double eta = -S.z / kj;
-    for (int64_t q = lane; q < 2 * Q * slot; q += WT) ring[q] = 0.0;
-    for (int64_t q = lane; q < 2 * slot; q += WT) Vs[q] = 0.0;
-    for (int64_t q = lane; q < slot; q += WT) {
+    for (int64_t q = tid; q < 2 * Q * slot; q += WT * NW) ring[q] = 0.0;
+    for (int64_t q = tid; q < 2 * slot; q += WT * NW) Vs[q] = 0.0;
+    for (int64_t q = tid; q < slot; q += WT * NW) {
       g[q] = 0.0;
       gp[q] = 0.0;
     }
-    wave_sync();
-    if (lane < CB && real_col) {
+    team_sync<NW>();
+    if (tid < CB && real_col) {
       const int64_t o = (int64_t)j * CW + jj;
       ring[o] = 1.0;             // order 0 at position 0
       ring[Q * slot + o] = 1.0;  // and its duplicate
       g[o] = 1.0;
     }
-    wave_sync();
+    team_sync<NW>();
     bool active = real_col;
     bool ncv = false;
     double t_prev = 1.0;
     for (int P = 1; P <= S.gl_terms; ++P) {
-      if (!wave_or(active ? 1 : 0)) break;
-      double *Vn = Vs + (P & 1) * slot;
-      const double *Vo = Vs + ((P - 1) & 1) * slot;
-      const double *d1 = ring + gl_pos(P - 1, Q) * slot;
-      const double *d2 = ring + gl_pos(P - 2, Q) * slot;
-      double *dn = ring + gl_pos(P, Q) * slot;
-      double *dd = dn + Q * slot;
+      if (!uni(wave_or(active ? 1 : 0))) break;
+      RM_G double *Vn = Vs + (P & 1) * slot;
+      const RM_G double *Vo = Vs + ((P - 1) & 1) * slot;
+      const RM_G double *d1 = ring + gl_pos(P - 1, Q) * slot;
+      const RM_G double *d2 = ring + gl_pos(P - 2, Q) * slot;
+      RM_G double *dn = ring + gl_pos(P, Q) * slot;
+      RM_G double *dd = dn + Q * slot;
       if (S.lmax > 0)  // V(P): orders P-1 .. P-lmax are consecutive slots
-        wave_gemm<2>(Vn, CW, S.gl_beta, S.lmax * n, d1, CW, n, CW,
+        team_gemm<NW, 2>(Vn, CW, as_g(S.gl_beta), S.lmax * n, d1, CW, n, CW,
                      S.lmax * n);
       double tmax = 0.0;
-      for (int q = lane; q < n * CB; q += WT) {
+      for (int q = tid; q < n * CB; q += WT * NW) {
         const int i = q / CB;
         const int64_t o = (int64_t)i * CW + jj;
         const double ei = S.e_thr[i];
@@ -262,6 +245,14 @@ __device__ int wave_gailitis_system(const SymDev &S, double Ee, double *Aug,
       }
       tmax = fmax(tmax, __shfl_xor(tmax, 16));
       tmax = fmax(tmax, __shfl_xor(tmax, 32));
+      if constexpr (NW > 1) {  // over the wavefronts, per column
+        RM_L double *tm = &W.cand[P & 1][0][0];
+        const int wv = team_wave<NW>();
+        if (lane_id() < CB) tm[wv * NB2 + jj] = tmax;
+        team_sync<NW>();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) tmax = fmax(tmax, tm[w * NB2 + jj]);
+      }
       bool add = false;
       if (active) {
         if (tmax > t_prev) {
@@ -277,7 +268,7 @@ __device__ int wave_gailitis_system(const SymDev &S, double Ee, double *Aug,
       }
       if (add) {
         const double m = -P * ir;
-        for (int q = lane; q < n * CB; q += WT) {
+        for (int q = tid; q < n * CB; q += WT * NW) {
           const int64_t o = (int64_t)(q / CB) * CW + jj;
           const double nr = dn[o], ni = dn[o + CB];
           g[o] += nr;
@@ -286,7 +277,7 @@ __device__ int wave_gailitis_system(const SymDev &S, double Ee, double *Aug,
           gp[o + CB] += m * ni;
         }
       }
-      wave_sync();
+      team_sync<NW>();
     }
     if (active) ncv = t_prev > kGlFlag;  // ended at gl_terms terms
     if (ncv) bits |= RM_E_ASYM_NOCONV;
@@ -296,7 +287,7 @@ __device__ int wave_gailitis_system(const SymDev &S, double Ee, double *Aug,
                       coulomb_phase(lj, eta);
     const double sq = 1.0 / sqrt(kj);
     const double cr = cos(th) * sq, ci = sin(th) * sq, tp = kj - eta * ir;
-    for (int q = lane; q < n * CB; q += WT) {
+    for (int q = tid; q < n * CB; q += WT * NW) {
       const int64_t o = (int64_t)(q / CB) * CW + jj;
       const double gr = g[o], gi = g[o + CB];
       const double hr = gp[o] - tp * gi, hi = gp[o + CB] + tp * gr;
@@ -307,57 +298,72 @@ __device__ int wave_gailitis_system(const SymDev &S, double Ee, double *Aug,
       Y[o] = real_col ? r * vr : 0.0;  // A C'
       Y[o + CB] = real_col ? r * vi : 0.0;  // A S'
     }
-    wave_sync();
-    wave_gemm<2>(X, CW, Kb, n, Y, CW, n, CW, n);
+    team_sync<NW>();
+    team_gemm<NW, 2>(X, CW, Kb, n, Y, CW, n, CW, n);
     if (real_col)
-      for (int q = lane; q < n * CB; q += WT) {
+      for (int q = tid; q < n * CB; q += WT * NW) {
         const int i = q / CB;
         const int64_t o = (int64_t)i * CW + jj;
         Aug[(int64_t)i * ld + j] = ring[o] - X[o];
         Aug[(int64_t)i * ld + n + j] = X[o + CB] - ring[o + CB];
       }
-    wave_sync();
+    team_sync<NW>();
   }
   return bits;
 }
 
-// Outer-region propagation of every symmetry that has sectors, one
-// wavefront per energy, before the matching kernel: R(a) -> R(A) in place,
-// and with the asymptotic expansion the whole matching system at A.
-// Sector failures are or-ed into status.
-__global__ __launch_bounds__(WT *WPB) void propagate_kernel(MatchLaunch L) {
-  __shared__ WaveLds lds[WPB];
-  const int lane = lane_id();
-  const int wv = threadIdx.x >> 6;
-  const int e = blockIdx.x * WPB + wv;
-  if (e >= L.m) return;
-  int bits = 0;
-  for (int s = 0; s < L.n_sym; ++s) {
-    const SymDev &S = L.syms[s];
-    if (S.n_sec <= 0) continue;
-    double *Aug = L.work + (int64_t)e * L.work_estride + L.work_off[s];
-    double *Kb = Aug + (int64_t)2 * S.n * S.n;
-    ChanSlot *ch = L.chan + (int64_t)e * L.chan_estride + L.chan_off[s];
-    if (wave_propagate(S, L.E[e], Aug, 2 * S.n, Kb, ch, lds[wv]))
-      bits |= RM_E_SINGULAR;
-    if (S.gl_terms > 0) {
-      const int no = count_open(S, L.E[e]);
-      if (no > 0) {
-        bits |= wave_channel_functions(S, L.E[e], ch);
-        wave_sync();
-        bits |= wave_gailitis_system(S, L.E[e], Aug, 2 * S.n, Kb, ch, no,
-                                     Aug + match_work_doubles(S.n));
-      }
-    }
-  }
-  bits = wave_or(bits);
-  if (lane == 0 && L.status && bits) atomicOr(&L.status[e], bits);
+// Outer-region propagation of one symmetry, one team per energy, before the
+// matching: R(a) -> R(A) in place.  Sector failures are or-ed into status.
+template <int NW, int NAMAX>
+__global__ __launch_bounds__(WT *NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void propagate_kernel(MatchLaunch L) {
+  __shared__ TeamLds<NW> lds;
+  RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
+  const SymDev &S = L.syms[L.sym];
+  const int e = blockIdx.x;
+  const Place P = place_of(L, S, e);
+  const int f = team_propagate<NW, NAMAX>(S, L.E[e], P.work, 2 * S.n,
+                                          P.work + (int64_t)2 * S.n * S.n, P.ch, W);
+  put_status(L, e, f ? RM_E_SINGULAR : 0);
 }
 
-hipError_t launch_propagate(const MatchLaunch &L, hipStream_t st) {
-  if (L.m <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((L.m + WPB - 1) / WPB);
-  hipLaunchKernelGGL(propagate_kernel, dim3(blocks), dim3(WT * WPB), 0, st, L);
+// The matching system at A from the asymptotic expansion, after the
+// propagation.
+template <int NW>
+__global__ __launch_bounds__(WT *NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void gailitis_kernel(MatchLaunch L) {
+  __shared__ TeamLds<NW> lds;
+  RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
+  const SymDev &S = L.syms[L.sym];
+  const int e = blockIdx.x;
+  const Place P = place_of(L, S, e);
+  const int no = count_open(S, L.E[e]);
+  if (no == 0) return;
+  int bits = team_channel_functions<NW>(S, L.E[e], P.ch);
+  team_sync<NW>();
+  bits |= team_gailitis_system(S, L.E[e], P.work, 2 * S.n,
+                               P.work + (int64_t)2 * S.n * S.n, P.ch, no,
+                               P.work + match_work_doubles(S.n), W);
+  put_status(L, e, bits);
+}
+
+// Teams of four up to 256 channels (the smallest symmetries too: a sector is
+// a chain of block steps that one wavefront alone takes longer over).
+hipError_t launch_propagate(const MatchLaunch &L0, hipStream_t st) {
+  if (L0.m <= 0) return hipSuccess;
+  MatchLaunch L = L0;
+  for (int q = 0; q < L.n_sym; ++q) {
+    if (!(L.h_outer[q] & 1)) continue;
+    const bool gl = L.h_outer[q] & 2;
+    L.sym = q;
+    if (L.h_n[q] <= 256) {
+      hipLaunchKernelGGL((propagate_kernel<4, 256>), dim3(L.m), dim3(WT * 4), 0, st, L);
+      if (gl) hipLaunchKernelGGL(gailitis_kernel<4>, dim3(L.m), dim3(WT * 4), 0, st, L);
+    } else {
+      hipLaunchKernelGGL((propagate_kernel<8, 4096>), dim3(L.m), dim3(WT * 8), 0, st, L);
+      if (gl) hipLaunchKernelGGL(gailitis_kernel<8>, dim3(L.m), dim3(WT * 8), 0, st, L);
+    }
+  }
   return hipGetLastError();
 }
 

@@ -436,7 +436,7 @@ static int free_sym(Sym *s);
 // A plan fixes the symmetries (ordered by cost, largest first), the chunk
 // length, the workspace layout and the pole-sum work-item tables, so that
 // the whole sweep is a fixed sequence of launches: per chunk one grouped
-// pole-sum launch per tile variant and one persistent matching launch.
+// pole-sum launch per tile variant and the matching's steps per symmetry.
 
 // [Aug n x 2n | K n x n | g n | v n | pivots n]: g and v serve
 // photoionization, the pivots (as int) the FP32 solve's refinement
@@ -472,12 +472,9 @@ struct Plan {
   double *work = nullptr;
   double *ext = nullptr;           // T step's complex-system pool (nullable)
   int64_t ext_estride = 0;         // doubles per slot
-  int *ext_flags = nullptr;        // one per slot, 0 = free
   int ext_slots = 0;
   bool want_t = true;              // the sweep forms T (set before building)
   ChanSlot *chan = nullptr;
-  int *counters = nullptr;         // one per chunk (match kernel)
-  int match_grid = 0;
   void *block = nullptr;           // all of the above and the tables
   bool owns_async = false;         // ... from the pool
   bool in_arena = false;           // tables and workspace in an Arena
@@ -498,6 +495,7 @@ struct Plan {
   bool aligned() const {
     return n_chunks <= 1 || C % ps_energy_group(PS_F64_GROUP) == 0;
   }
+  std::vector<int> h_n, h_outer;    // channels; 1 sectors, 2 the expansion
   bool propagate = false;           // some symmetry has outer sectors
   // damped photoionization: per-symmetry offsets of R_re and R_im
   bool damped = false;
@@ -522,9 +520,7 @@ static void plan_free_device(Plan &p) {
     p.d_work_off = p.d_chan_off = nullptr;
     p.work = nullptr;
     p.ext = nullptr;
-    p.ext_flags = nullptr;
     p.chan = nullptr;
-    p.counters = nullptr;
     return;
   }
   p.sets.clear();
@@ -532,7 +528,6 @@ static void plan_free_device(Plan &p) {
   p.d_work_off = p.d_chan_off = nullptr;
   p.d_rre_off = p.d_rim_off = nullptr;
   p.ext = nullptr;
-  p.ext_flags = nullptr;
   if (p.block) {
     if (p.owns_async)
       (void)hipFreeAsync(p.block, p.alloc_stream);
@@ -542,7 +537,6 @@ static void plan_free_device(Plan &p) {
   p.block = nullptr;
   p.work = nullptr;
   p.chan = nullptr;
-  p.counters = nullptr;
 }
 
 // ---- autotuner: fastest mixed tile variant per (n, N_H, precision)
@@ -814,16 +808,6 @@ static void build_items(const Plan &p, int variant, int64_t m,
   }
 }
 
-static int match_grid_size() {
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, dev) == hipSuccess)
-      cus = prop.multiProcessorCount;
-  }
-  return cus * 4;
-}
-
 // Workspace budget of a sweep: at least `base` bytes, else up to 40 % of
 // the device memory free now (at most 96 GB), so that large symmetries
 // still get enough energies per chunk to fill the GPU with wavefronts.
@@ -931,18 +915,20 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
              (8.0 * p.ext_estride + 4.0) * p.ext_slots > 0.25 * (double)arena->cap)
         p.ext_slots /= 2;
   }
-  p.match_grid = match_grid_size();
   p.h_work_off = woff;
-  for (const Sym *q : v) p.propagate = p.propagate || q->n_sec > 0;
+  for (const Sym *q : v) {
+    p.propagate = p.propagate || q->n_sec > 0;
+    p.h_n.push_back(q->n);
+    p.h_outer.push_back(q->n_sec > 0 ? 1 + (q->gl_terms > 0 ? 2 : 0) : 0);
+  }
   // workspace and channel slots
   const double per_energy = 8.0 * wacc + 32.0 * cacc;
   int64_t C;
   if (arena) {
     // what the arena holds after the tables (bounded by the item tables of
-    // the largest chunk: at most one item per tile and energy, 16 bytes,
-    // plus a counter per chunk)
+    // the largest chunk: at most one item per tile and energy, 16 bytes)
     const double tables = (double)sd.size() * (sizeof(SymDev) + 16) + 65536.0;
-    // less the complex-system pool and its flags
+    // less the complex-system pool
     const double room = (double)arena->cap - tables -
                         (8.0 * p.ext_estride + 4.0) * p.ext_slots - 256.0;
     double tiles = 0.0;
@@ -955,7 +941,7 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
     }
     // per energy: workspace, slots, and the pole-sum items of a full and a
     // tail chunk (one per tile and energy group, at most one per energy),
-    // plus the per-chunk counters for M / C chunks
+    // with the alignment of the pieces
     const double per = per_energy + 2.0 * tiles * sizeof(PsItem) + 512.0;
     C = room > per ? (int64_t)(room / per) : 0;
     if (o.chunk > 0) C = std::min<int64_t>(C, o.chunk);
@@ -1036,19 +1022,16 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
                                          : RM_ERR_HIP,
                 "plan tables: %s", hipGetErrorString(e));
   const size_t wbytes = (size_t)(C * wacc) * sizeof(double);
-  // the pool and its flags after the workspace, in one allocation
-  const size_t xbytes = (size_t)(p.ext_slots * p.ext_estride) * sizeof(double) +
-                        (size_t)p.ext_slots * sizeof(int);
+  // the complex-system pool after the workspace, in one allocation
+  const size_t xbytes = (size_t)(p.ext_slots * p.ext_estride) * sizeof(double);
   const size_t cbytes = (size_t)(C * cacc) * sizeof(ChanSlot);
-  const size_t kbytes = (size_t)std::max(1, p.n_chunks) * sizeof(int);
   p.owns_async = async && !arena;
   p.alloc_stream = st;
   // the complex-system pool is carved from the end of the workspace's own
   // allocation (a part per energy there timed 4 % faster at 200 channels
   // than in an allocation of its own)
   if (arena) {
-    e = arena->take(&p.work, wbytes + xbytes) && arena->take(&p.chan, cbytes) &&
-                arena->take(&p.counters, kbytes)
+    e = arena->take(&p.work, wbytes + xbytes) && arena->take(&p.chan, cbytes)
             ? hipSuccess
             : hipErrorOutOfMemory;
     if (e != hipSuccess)
@@ -1056,15 +1039,13 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
                   "%zu-byte scratch", wbytes + xbytes + cbytes, arena->cap);
   } else {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const size_t at_chan = up(wbytes + xbytes), at_cnt = at_chan + up(cbytes);
-    const size_t at_tab = at_cnt + up(kbytes);
+    const size_t at_chan = up(wbytes + xbytes), at_tab = at_chan + up(cbytes);
     e = async ? pool_alloc(&p.block, at_tab + blob.size(), st)
               : device_malloc(&p.block, at_tab + blob.size());
     if (e == hipSuccess) {
       char *base = (char *)p.block;
       p.work = (double *)base;
       p.chan = (ChanSlot *)(base + at_chan);
-      p.counters = (int *)(base + at_cnt);
       for (auto &x : pieces) *x.first = base + at_tab + x.second;
       e = hipMemcpyAsync(base + at_tab, blob.data(), blob.size(),
                          hipMemcpyHostToDevice, st);
@@ -1072,10 +1053,7 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
       if (e == hipSuccess) e = hipStreamSynchronize(st);
     }
   }
-  if (e == hipSuccess && p.ext_slots) {
-    p.ext = p.work + C * wacc;
-    p.ext_flags = (int *)(p.ext + (int64_t)p.ext_slots * p.ext_estride);
-  }
+  if (e == hipSuccess && p.ext_slots) p.ext = p.work + C * wacc;
   if (e != hipSuccess)
     return fail(e == hipErrorOutOfMemory ? RM_ERR_NOMEM : RM_ERR_HIP,
                 "workspace of %zu bytes: %s", wbytes + xbytes + cbytes,
@@ -1089,8 +1067,6 @@ static int plan_enqueue(Plan &p, hipStream_t st) {
   if (p.omega) RM_HIP(launch_fill(p.omega, p.M * P, 0.0, st));
   if (p.status) RM_HIP(launch_fill_i32(p.status, p.M, 0, st));
   if (p.sigma) RM_HIP(launch_fill(p.sigma, p.M, 0.0, st));
-  RM_HIP(launch_fill_i32(p.counters, std::max(1, p.n_chunks), 0, st));
-  if (p.ext_flags) RM_HIP(launch_fill_i32(p.ext_flags, p.ext_slots, 0, st));
   for (int c = 0; c < p.n_chunks; ++c) {
     const int64_t c0 = (int64_t)c * p.C;
     const int64_t m = std::min(p.C, p.M - c0);
@@ -1159,7 +1135,6 @@ static int plan_enqueue(Plan &p, hipStream_t st) {
     L.work_off = p.d_work_off;
     L.ext = p.ext;
     L.ext_estride = p.ext_estride;
-    L.ext_flags = p.ext_flags;
     L.ext_slots = p.ext_slots;
     L.chan = p.chan;
     L.chan_estride = p.chan_estride;
@@ -1174,13 +1149,11 @@ static int plan_enqueue(Plan &p, hipStream_t st) {
     L.do_t = p.do_t;
     L.sigma = p.sigma ? p.sigma + c0 : nullptr;
     L.e0 = p.e0;
-    L.counter = p.counters + c;
-    L.grid = p.match_grid;
     L.solve_fp32 = p.o.solve_fp32;
     L.refine_iters = p.o.refine_iters;
     L.damped = p.damped ? 1 : 0;
-    L.n_max = 0;
-    for (const Sym *q : p.syms) L.n_max = std::max(L.n_max, q->n);
+    L.h_n = p.h_n.data();
+    L.h_outer = p.h_outer.data();
     if (p.propagate) {
       StageTimer tp(7, st);
       RM_HIP(launch_propagate(L, st));
@@ -1829,10 +1802,7 @@ int rm_collision_strengths(rm_sym_t sym, const double *K, const int32_t *n_open,
   while (slots > 1 && 8.0 * slots * (double)xs > 16.0e9) slots /= 2;
   DevBuf work, tabs, chan, ext;
   if ((rc = dev_alloc(work, (size_t)(C * ws) * sizeof(double), st))) return rc;
-  if ((rc = dev_alloc(ext, (size_t)(slots * xs) * sizeof(double) + slots * sizeof(int), st)))
-    return rc;
-  int *ext_flags = (int *)((double *)ext.p + (int64_t)slots * xs);
-  RM_HIP(launch_fill_i32(ext_flags, slots, 0, st));
+  if ((rc = dev_alloc(ext, (size_t)(slots * xs) * sizeof(double), st))) return rc;
   if ((rc = dev_alloc(chan, (size_t)(C * s.n) * sizeof(ChanSlot), st))) return rc;
   if ((rc = dev_alloc(tabs, sizeof(SymDev) + sizeof(int64_t), st))) return rc;
   const SymDev sd = s.dev();
@@ -1853,9 +1823,8 @@ int rm_collision_strengths(rm_sym_t sym, const double *K, const int32_t *n_open,
     L.work_estride = ws;
     L.ext = (double *)ext.p;
     L.ext_estride = xs;
-    L.ext_flags = ext_flags;
     L.ext_slots = slots;
-    L.n_max = s.n;
+    L.h_n = &s.n;
     L.work_off = (const int64_t *)((char *)tabs.p + sizeof(SymDev));
     L.chan = (ChanSlot *)chan.p;           // rank table of the K input
     L.chan_estride = s.n;

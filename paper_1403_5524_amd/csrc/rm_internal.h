@@ -17,11 +17,9 @@ constexpr int kPolePad = 64;
 constexpr double kPadPole = 1.0e30;  // padding poles sit far from any energy
 // The T step's well-conditioned route (the real 2n x 2n form of
 // (1 - iK) W = 1 with its right-hand sides, 6 n^2 doubles) runs at few
-// energies, so its buffers form a small pool of slots that a wavefront
-// takes by compare-and-swap on a flag and gives back when done; with every
-// slot taken the energy takes the route through Z = L^-1 K instead (no
-// wavefront ever waits).
-constexpr int kMatchWpb = 4;     // wavefronts per matching workgroup
+// energies, so its buffers form a small pool: the team of slot q takes every
+// energy q, q + slots, ... of the chunk that needs the route.  Without a pool
+// those energies take the route through Z = L^-1 K instead.
 constexpr int kTExtSlots = 64;   // pool slots of an allocating sweep
 constexpr int kTExtSlotsArena = 16;  // of a sweep that may not allocate
 __host__ __device__ inline int64_t t_ext_doubles(int n) {
@@ -235,12 +233,14 @@ int ps_units(int variant, int64_t m, bool aligned);
 // Tile items of one symmetry for a variant: (x, y) pairs, in order.
 void ps_tiles(const Sym &s, int variant, std::vector<std::pair<int, int>> &out);
 
-// Channel functions, matching, K, T and Omega: one wavefront per energy,
-// looping over every symmetry (so it owns that energy's Omega row).  With a
-// counter the grid is persistent.
+// Channel functions, matching, K, T and Omega: one team of wavefronts per
+// energy, the symmetries in turn (so an energy's Omega row has one owner).
 struct MatchLaunch {
   const SymDev *syms;
   int n_sym;
+  const int *h_n;             // host [n_sym]: channels of each symmetry
+  const int *h_outer;         // host [n_sym]: 1 sectors, 2 and the expansion
+  int sym;                    // the symmetry of a kernel (set per launch)
   const double *E;
   int m;
   // photoionization: the dipole pole sum g of each symmetry sits after its
@@ -262,8 +262,6 @@ struct MatchLaunch {
   int n_target_out;
   int32_t *status;            // nullable
   int do_t;
-  int *counter;               // nullable
-  int grid;
   int solve_fp32;             // FP32 factorisation refined in FP64
   int refine_iters;           // at most this many corrections
   // radiation-damped photoionization: per symmetry the workspace holds the
@@ -272,13 +270,14 @@ struct MatchLaunch {
   int damped;
   // the T step's complex-system pool (nullable): ext_slots slots of
   // ext_estride doubles (at least t_ext_doubles(n) of every symmetry) at
-  // ext + slot * ext_estride, slot q free while ext_flags[q] == 0 (the
-  // flags start at zero)
+  // ext + slot * ext_estride
   double *ext;
   int64_t ext_estride;
-  int *ext_flags;
   int ext_slots;
-  int n_max;                  // the largest symmetry's channels (kernel choice)
+};
+enum MatchStep {
+  STEP_ASSEMBLE, STEP_ASSEMBLE_DAMPED, STEP_LU, STEP_FP32, STEP_K_OUT, STEP_T,
+  STEP_T_COMPLEX, STEP_T_Z, STEP_PHOTO, STEP_DAMPED_SIGMA
 };
 hipError_t launch_match(const MatchLaunch &L, hipStream_t st);
 // R(a) -> R(A) for the symmetries with outer-region sectors (same launch
