@@ -831,20 +831,63 @@ void t_kernel(MatchLaunch L) {
 
 // The T step's route for large K: (1 - iK) W = 1 as the real system
 // [1 K; -K 1] [X; Y] = [1; 0] (2 no x 3 no, leading dimension 3 no) by the
-// team's LU, in the pool's slot blockIdx.x, which takes every gridDim.x-th
-// energy of the chunk.
+// team's LU, in the pool's slot blockIdx.x.  A team alone on a CU is a serial
+// chain (2.6 ms at 200 open channels) and few energies take it, so what counts
+// is that no slot gets two while others get none: the q-th flagged energy of
+// the chunk goes to slot q mod the slots, each team counting the flags for
+// itself.  (With every slots-th energy to a slot, flagged or not, two of about
+// twenty met at 200 channels: 5.2 ms of a 29 ms sweep.)
 template <int NW, int NAMAX>
 __global__ __launch_bounds__(WT *NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void t_complex_kernel(MatchLaunch L) {
   __shared__ TeamLds<NW> lds;
   RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
   const SymDev &S = L.syms[L.sym];
-  const int n = S.n, ld = 2 * n;
+  const int n = S.n, ld = 2 * n, m = L.m;
   RM_G double *ext = as_g(L.ext + (int64_t)blockIdx.x * L.ext_estride);
+  constexpr int FB = 8;  // batches of 64 flags in flight
+  int skip = blockIdx.x;  // flagged energies before this slot's next one
+  unsigned long long flags = 0;
+  int eb = -WT, cached = 0;
+  unsigned int mine = 0;  // this lane's flags of the next `cached` batches
 #pragma unroll 1
-  for (int e = blockIdx.x; e < L.m; e += gridDim.x) {
+  for (;;) {
+    // the next energy of this slot: skip flagged ones
+    int e = -1;
+#pragma unroll 1
+    while (e < 0) {
+      if (flags == 0) {
+        eb += WT;
+        if (eb >= m) break;
+        if (cached == 0) {
+          mine = 0;
+#pragma unroll
+          for (int u = 0; u < FB; ++u) {
+            const int f = eb + u * WT + lane_id();
+            const Place P = place_of(L, S, min(f, m - 1));
+            mine |= (f < m && *P.flag != 0 ? 1u : 0u) << u;
+          }
+          cached = FB;
+        }
+        flags = __ballot(mine & 1u);
+        mine >>= 1;
+        --cached;
+        continue;
+      }
+      const int have = __popcll(flags);
+      if (have <= skip) {
+        skip -= have;
+        flags = 0;
+        continue;
+      }
+      for (; skip > 0; --skip) flags &= flags - 1;
+      e = eb + __builtin_ctzll(flags);
+      flags &= flags - 1;
+      skip = gridDim.x - 1;
+    }
+    e = uni(e);
+    if (e < 0) break;
     const Place P = place_of(L, S, e);
-    if (uni(*P.flag) == 0) continue;
     const int no = count_open(S, L.E[e]);
     RM_G double *Aug = P.work, *Kb = P.work + (int64_t)2 * n * n;
     const int l3 = 3 * no;

@@ -18,8 +18,8 @@ constexpr double kPadPole = 1.0e30;  // padding poles sit far from any energy
 // The T step's well-conditioned route (the real 2n x 2n form of
 // (1 - iK) W = 1 with its right-hand sides, 6 n^2 doubles) runs at few
 // energies, so its buffers form a small pool: the team of slot q takes every
-// energy q, q + slots, ... of the chunk that needs the route.  Without a pool
-// those energies take the route through Z = L^-1 K instead.
+// q-th, (q + slots)-th, ... energy of the chunk that needs the route.  Without
+// a pool those energies take the route through Z = L^-1 K instead.
 constexpr int kTExtSlots = 64;   // pool slots of an allocating sweep
 constexpr int kTExtSlotsArena = 16;  // of a sweep that may not allocate
 __host__ __device__ inline int64_t t_ext_doubles(int n) {
