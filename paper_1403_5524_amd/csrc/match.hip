@@ -11,7 +11,9 @@ hipError_t launch_team_w8(const MatchLaunch &L, MatchStep step, hipStream_t st);
 
 // Team size of a step whose largest matrix has `rows` rows.  One wavefront
 // holds the register panel of 64 rows, four that of 256; above, eight (two
-// rows per thread up to 1024 rows).
+// rows per thread up to 1024 rows).  Eight for 129 to 256 rows where a chunk
+// has no more than a team per CU is no faster (200 channels, 256 energies: LU
+// 1.01 ms against 0.88, T 0.76 against 0.81, 20 sectors 25.8 against 25.4).
 static hipError_t launch_step(const MatchLaunch &L, MatchStep step, int rows,
                               hipStream_t st) {
   if (rows <= 64) return launch_team_w1(L, step, st);
@@ -26,6 +28,9 @@ hipError_t launch_match(const MatchLaunch &L0, hipStream_t st) {
   auto step = [&](MatchStep s, int rows) {
     if (e == hipSuccess) e = launch_step(L, s, rows, st);
   };
+  const int n_max = *std::max_element(L0.h_n, L0.h_n + L0.n_sym);
+  const bool pool = L.do_t && !L.damped && !L.sigma && L.ext &&
+                    L.ext_slots > 0 && t_ext_doubles(n_max) <= L.ext_estride;
   for (int q = 0; q < L0.n_sym; ++q) {
     const int n = L0.h_n[q];
     L.sym = q;
@@ -48,11 +53,9 @@ hipError_t launch_match(const MatchLaunch &L0, hipStream_t st) {
       continue;
     }
     step(STEP_T, n);
-    if (L.ext && L.ext_slots > 0 && t_ext_doubles(n) <= L.ext_estride)
-      step(STEP_T_COMPLEX, 2 * n);
-    else
-      step(STEP_T_Z, n);
+    if (!pool) step(STEP_T_Z, n);
   }
+  if (pool) step(STEP_T_COMPLEX, 2 * n_max);
   return e;
 }
 

@@ -627,10 +627,11 @@ struct Place {
   RM_G ChanSlot *ch;
   RM_G int *flag;  // the last word of the channel slots: the energy's route
 };
-__device__ inline Place place_of(const MatchLaunch &L, const SymDev &S, int e) {
+__device__ inline Place place_of(const MatchLaunch &L, const SymDev &S, int sym,
+                                 int e) {
   Place p;
-  p.work = as_g(L.work + (int64_t)e * L.work_estride + L.work_off[L.sym]);
-  p.ch = as_g(L.chan + (int64_t)e * L.chan_estride + L.chan_off[L.sym]);
+  p.work = as_g(L.work + (int64_t)e * L.work_estride + L.work_off[sym]);
+  p.ch = as_g(L.chan + (int64_t)e * L.chan_estride + L.chan_off[sym]);
   p.flag = (RM_G int *)(p.ch + S.n) - 1;
   return p;
 }
@@ -648,7 +649,7 @@ template <int NW, bool DAMPED>
 __global__ __launch_bounds__(WT *NW) void assemble_kernel(MatchLaunch L) {
   const SymDev &S = L.syms[L.sym];
   const int e = blockIdx.x, n = S.n;
-  const Place P = place_of(L, S, e);
+  const Place P = place_of(L, S, L.sym, e);
   const double Ee = L.E[e];
   const int no = count_open(S, Ee);
   if (L.n_open_out && threadIdx.x == 0) L.n_open_out[e] = no;
@@ -674,7 +675,7 @@ void lu_kernel(MatchLaunch L) {
   RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
   const SymDev &S = L.syms[L.sym];
   const int e = blockIdx.x, n = S.n;
-  const Place P = place_of(L, S, e);
+  const Place P = place_of(L, S, L.sym, e);
   const int no = count_open(S, L.E[e]);
   if (no == 0) return;
   if (L.solve_fp32 && uni(*P.flag) == 0) return;  // refined from FP32 factors
@@ -691,7 +692,7 @@ void solve_fp32_kernel(MatchLaunch L) {
   RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
   const SymDev &S = L.syms[L.sym];
   const int e = blockIdx.x, n = S.n;
-  const Place P = place_of(L, S, e);
+  const Place P = place_of(L, S, L.sym, e);
   const int no = count_open(S, L.E[e]);
   if (no == 0) return;
   const int bits = team_solve_fp32<NW, NAMAX>(
@@ -737,7 +738,7 @@ template <int NW>
 __global__ __launch_bounds__(WT *NW) void k_out_kernel(MatchLaunch L) {
   const SymDev &S = L.syms[L.sym];
   const int e = blockIdx.x, n = S.n, ld = 2 * n;
-  const Place P = place_of(L, S, e);
+  const Place P = place_of(L, S, L.sym, e);
   const int no = count_open(S, L.E[e]);
   RM_G int *rank = (RM_G int *)P.ch;  // the channel slots are consumed
   RM_G double *Ko = as_g(L.K_out + (int64_t)e * n * n);
@@ -768,7 +769,7 @@ void t_kernel(MatchLaunch L) {
   RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
   const SymDev &S = L.syms[L.sym];
   const int e = blockIdx.x, n = S.n, ld = 2 * n, tid = team_tid<NW>();
-  const Place P = place_of(L, S, e);
+  const Place P = place_of(L, S, L.sym, e);
   const int no = count_open(S, L.E[e]);
   if (no == 0) {
     if (tid == 0) *P.flag = 0;
@@ -831,19 +832,21 @@ void t_kernel(MatchLaunch L) {
 
 // The T step's route for large K: (1 - iK) W = 1 as the real system
 // [1 K; -K 1] [X; Y] = [1; 0] (2 no x 3 no, leading dimension 3 no) by the
-// team's LU, in the pool's slot blockIdx.x.  A team alone on a CU is a serial
-// chain (2.6 ms at 200 open channels) and few energies take it, so what counts
-// is that no slot gets two while others get none: the q-th flagged energy of
-// the chunk goes to slot q mod the slots, each team counting the flags for
-// itself.  (With every slots-th energy to a slot, flagged or not, two of about
-// twenty met at 200 channels: 5.2 ms of a 29 ms sweep.)
+// team's LU, in the pool's slot blockIdx.x, for every symmetry of the launch.
+// A team alone on a CU is a serial chain (2.6 ms at 200 open channels, 6.3 at
+// 400) and few energies take it, so what counts is that chains run side by
+// side: the q-th energy of the chunk with a flag in any symmetry goes to slot
+// q mod the slots, each team counting the flags for itself, and its symmetries
+// follow each other in that team (one owner of the energy's Omega row).  With
+// every slots-th energy to a slot, flagged or not, two of about twenty met at
+// 200 channels, 5.2 ms of a 29 ms sweep; with a launch per symmetry a plan of
+// eight symmetries up to 400 channels spent 20 ms here, now 12.3.
 template <int NW, int NAMAX>
 __global__ __launch_bounds__(WT *NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void t_complex_kernel(MatchLaunch L) {
   __shared__ TeamLds<NW> lds;
   RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
-  const SymDev &S = L.syms[L.sym];
-  const int n = S.n, ld = 2 * n, m = L.m;
+  const int m = L.m;
   RM_G double *ext = as_g(L.ext + (int64_t)blockIdx.x * L.ext_estride);
   constexpr int FB = 8;  // batches of 64 flags in flight
   int skip = blockIdx.x;  // flagged energies before this slot's next one
@@ -861,11 +864,15 @@ void t_complex_kernel(MatchLaunch L) {
         if (eb >= m) break;
         if (cached == 0) {
           mine = 0;
+#pragma unroll 1
+          for (int q = 0; q < L.n_sym; ++q) {
+            const SymDev &S = L.syms[q];
 #pragma unroll
-          for (int u = 0; u < FB; ++u) {
-            const int f = eb + u * WT + lane_id();
-            const Place P = place_of(L, S, min(f, m - 1));
-            mine |= (f < m && *P.flag != 0 ? 1u : 0u) << u;
+            for (int u = 0; u < FB; ++u) {
+              const int f = eb + u * WT + lane_id();
+              const Place P = place_of(L, S, q, min(f, m - 1));
+              mine |= (f < m && *P.flag != 0 ? 1u : 0u) << u;
+            }
           }
           cached = FB;
         }
@@ -887,32 +894,39 @@ void t_complex_kernel(MatchLaunch L) {
     }
     e = uni(e);
     if (e < 0) break;
-    const Place P = place_of(L, S, e);
-    const int no = count_open(S, L.E[e]);
-    RM_G double *Aug = P.work, *Kb = P.work + (int64_t)2 * n * n;
-    const int l3 = 3 * no;
-    team_each<NW>(
-        no, no, [&](int i, int j) { return Kb[(int64_t)i * n + j]; },
-        [&](int i, int j, double k) {
-          const double one = i == j ? 1.0 : 0.0;
-          RM_G double *r = ext + (int64_t)i * l3 + j;
-          RM_G double *s = ext + (int64_t)(no + i) * l3 + j;
-          r[0] = one;
-          r[no] = k;
-          r[2 * no] = one;
-          s[0] = -k;
-          s[no] = one;
-          s[2 * no] = 0.0;
-        });
-    team_sync<NW>();
-    int bits = team_lu_solve<NW, NAMAX>(ext, 2 * no, l3, no, W) ? RM_E_SINGULAR : 0;
-    // X = A (rows [0, no)), Y (rows [no, 2 no)) of the solution; V in K's place
-    if (team_omega<NW>(S, L.n_target_out, ext + (int64_t)no * l3 + 2 * no, l3,
-                       ext + 2 * no, l3, true, Kb, n, no,
-                       as_g(L.omega + (int64_t)e * L.omega_stride)))
-      bits |= RM_E_NONFINITE;
-    put_status(L, e, bits);
-    team_sync<NW>();
+#pragma unroll 1
+    for (int q = 0; q < L.n_sym; ++q) {
+      const SymDev &S = L.syms[q];
+      const Place P = place_of(L, S, q, e);
+      if (uni(*P.flag) == 0) continue;
+      const int n = uni(S.n), no = uni(count_open(S, L.E[e]));
+      RM_G double *Kb = P.work + (int64_t)2 * n * n;
+      const int l3 = 3 * no;
+      team_each<NW>(
+          no, no, [&](int i, int j) { return Kb[(int64_t)i * n + j]; },
+          [&](int i, int j, double k) {
+            const double one = i == j ? 1.0 : 0.0;
+            RM_G double *r = ext + (int64_t)i * l3 + j;
+            RM_G double *s = ext + (int64_t)(no + i) * l3 + j;
+            r[0] = one;
+            r[no] = k;
+            r[2 * no] = one;
+            s[0] = -k;
+            s[no] = one;
+            s[2 * no] = 0.0;
+          });
+      team_sync<NW>();
+      int bits =
+          team_lu_solve<NW, NAMAX>(ext, 2 * no, l3, no, W) ? RM_E_SINGULAR : 0;
+      // X = A (rows [0, no)), Y (rows [no, 2 no)) of the solution; V in K's
+      // place
+      if (team_omega<NW>(S, L.n_target_out, ext + (int64_t)no * l3 + 2 * no, l3,
+                         ext + 2 * no, l3, true, Kb, n, no,
+                         as_g(L.omega + (int64_t)e * L.omega_stride)))
+        bits |= RM_E_NONFINITE;
+      put_status(L, e, bits);
+      team_sync<NW>();
+    }
   }
 }
 
@@ -925,7 +939,7 @@ void t_z_kernel(MatchLaunch L) {
   RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
   const SymDev &S = L.syms[L.sym];
   const int e = blockIdx.x, n = S.n, ld = 2 * n;
-  const Place P = place_of(L, S, e);
+  const Place P = place_of(L, S, L.sym, e);
   if (uni(*P.flag) == 0) return;
   const int no = count_open(S, L.E[e]);
   RM_G double *Aug = P.work, *Kb = P.work + (int64_t)2 * n * n;
@@ -994,7 +1008,7 @@ void photo_kernel(MatchLaunch L) {
   RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
   const SymDev &S = L.syms[L.sym];
   const int e = blockIdx.x, n = S.n, ld = 2 * n, tid = team_tid<NW>();
-  const Place P = place_of(L, S, e);
+  const Place P = place_of(L, S, L.sym, e);
   const int no = count_open(S, L.E[e]);
   if (no == 0) return;
   RM_G double *Aug = P.work, *Kb = P.work + (int64_t)2 * n * n;
@@ -1042,7 +1056,7 @@ __global__ __launch_bounds__(WT *NW) void damped_sigma_kernel(MatchLaunch L) {
   RM_L TeamLds<NW> &W = *(RM_L TeamLds<NW> *)&lds;
   const SymDev &S = L.syms[L.sym];
   const int e = blockIdx.x, n = S.n, ld = 2 * n + 2;
-  const Place P = place_of(L, S, e);
+  const Place P = place_of(L, S, L.sym, e);
   const int no = count_open(S, L.E[e]);
   if (no == 0) return;
   double s2 = 0.0;
