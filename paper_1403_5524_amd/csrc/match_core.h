@@ -141,9 +141,8 @@ __device__ __forceinline__ void team_copy(RM_G double *dst, int dl, const RM_G d
 // FP64 emulation).  That takes a slot of 6 n^2 doubles from the launch's
 // pool; without one the energy takes the route through Z = L^-1 K
 // (Q = Z^T Z, Y = L^-T Z), whose error grows more slowly than the A route's
-// but still with |K|^2; the latter also serves when every slot of the
-// complex route's buffer pool is taken.  At 200 channels about 0.5 % of a
-// uniform mesh's energies are above the threshold.
+// but still with |K|^2.  At 200 channels about 0.5 % of a uniform mesh's
+// energies are above the threshold.
 constexpr double kTInvMax = 1e8;
 
 // Factor the jb x jb (jb <= 32) diagonal block at (j0, j0) of A = L L^T in

@@ -1,7 +1,5 @@
-// Outer-region propagation kernel.  It has a translation unit of its own so
-// that the team linear algebra it shares with the matching kernel (LU, GEMM)
-// is compiled separately for each kernel: sharing those routines in one unit
-// changed the matching kernel's register allocation.
+// Outer-region propagation and asymptotic expansion, on the team linear algebra
+// of the matching.
 #include "match_core.h"
 
 namespace rmx {
@@ -139,7 +137,7 @@ __device__ double coulomb_phase(int l, double eta) {
 __device__ inline int gl_pos(int p, int Q) { return ((-p) % Q + Q) % Q; }
 
 // The matching system at A with the expansion's solutions, in place of the
-// one the matching kernel assembles from Coulomb functions: R(A) in Aug's
+// one the matching assembles from Coulomb functions: R(A) in Aug's
 // left half on entry (copied to Kb), closed channels' functions in ch, the
 // open channels j < no in blocks of kGlCols columns (thread t serves column
 // t mod kGlCols of a block).  Per block and order one team GEMM forms

@@ -1,16 +1,19 @@
 // Dense linear algebra of one energy by a team of NW wavefronts.
 //
-// A team is one workgroup of NW wavefronts.  All matrices are row-major in a per-energy global workspace.  The work of a
-// routine is split by output tiles, column chunks or rows over the team's
-// wavefronts, so every element sees the same operations in the same order
-// whatever NW is; the routines end with the team's barrier.
+// A team is one workgroup of NW wavefronts.  All matrices are row-major in a
+// per-energy global workspace.  The work of a routine is split by output
+// tiles, column chunks or rows over the team's wavefronts, so every element
+// sees the same operations in the same order whatever NW is; the routines end
+// with the team's barrier.
 //
 // What bounds it: at one wavefront per energy, two per SIMD, 2048 energies
 // were in flight and their 0.96 MB workspaces (200 channels) streamed through
 // HBM between the block steps: 30.8 MB and 6.0 us per energy.  A team keeps a
 // quarter or an eighth as many energies in flight, reads each panel once per
 // team through the CU's own cache, and spreads the serial phases (pivot
-// search, diagonal blocks) over as many SIMDs.
+// search, diagonal blocks) over as many SIMDs: 8.7 MB and 3.9 us per energy
+// (LU 2.1, T step 1.5, assembly 0.3) at 4096 energies, 2.4 TB/s in the LU where
+// a copy reaches 4.3.
 //
 // Every pass over memory is written as "issue all loads of a batch, then
 // compute, then store": the compiler cannot move a load above a store it
