@@ -624,14 +624,17 @@ __device__ __forceinline__ void team_assemble_damped(RM_G double *Sys,
 struct Place {
   RM_G double *work;
   RM_G ChanSlot *ch;
-  RM_G int *flag;  // the last word of the channel slots: the energy's route
+  // the energy's route: a word of its own, behind the FP32 solve's n pivots in
+  // the room of n doubles at the workspace's end (the channel slots are read by
+  // the steps after the solve)
+  RM_G int *flag;
 };
 __device__ inline Place place_of(const MatchLaunch &L, const SymDev &S, int sym,
                                  int e) {
   Place p;
   p.work = as_g(L.work + (int64_t)e * L.work_estride + L.work_off[sym]);
   p.ch = as_g(L.chan + (int64_t)e * L.chan_estride + L.chan_off[sym]);
-  p.flag = (RM_G int *)(p.ch + S.n) - 1;
+  p.flag = (RM_G int *)(p.work + (int64_t)3 * S.n * S.n + 2 * S.n) + S.n;
   return p;
 }
 
@@ -696,7 +699,6 @@ void solve_fp32_kernel(MatchLaunch L) {
   if (no == 0) return;
   const int bits = team_solve_fp32<NW, NAMAX>(
       L.refine_iters, n, P.work, P.work + (int64_t)2 * n * n, P.ch, no, W);
-  team_sync<NW>();  // the flag takes the place of a channel value
   if (threadIdx.x == 0) *P.flag = (bits & RM_E_REFINE_NOCONV) ? 1 : 0;
   put_status(L, e, bits);
 }

@@ -438,8 +438,9 @@ static int free_sym(Sym *s);
 // the whole sweep is a fixed sequence of launches: per chunk one grouped
 // pole-sum launch per tile variant and the matching's steps per symmetry.
 
-// [Aug n x 2n | K n x n | g n | v n | pivots n]: g and v serve
-// photoionization, the pivots (as int) the FP32 solve's refinement
+// [Aug n x 2n | K n x n | g n | v n | n]: g and v serve photoionization, the
+// last n doubles hold, as int, the n pivots of the FP32 solve's refinement and
+// behind them the energy's route
 static int64_t work_doubles(int n) { return match_work_doubles(n); }
 // damped photoionization: [2n x 2n real driven system, leading dimension
 // 2n + 2 | R_re n x n | R_im n x n | g_re n | g_im n]
