@@ -557,7 +557,7 @@ int rm_inner_region(const rm_inner_desc *d, double *E_pole, double *w,
   char *ws = nullptr;
   const size_t bytes = ndbl * sizeof(double) +
                        ((size_t)n + (size_t)npair) * sizeof(int32_t) + 64;
-  hipError_t e = hipMalloc((void **)&ws, bytes);
+  hipError_t e = device_malloc((void **)&ws, bytes);
   if (e != hipSuccess)
     return in_fail(e == hipErrorOutOfMemory ? RM_ERR_NOMEM : RM_ERR_HIP,
                    std::string(fn) + ": " + hipGetErrorString(e));

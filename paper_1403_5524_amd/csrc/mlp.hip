@@ -19,7 +19,7 @@
 #include <new>
 #include <vector>
 
-#include "../../include/rmatrix.h"
+#include "rm_internal.h"
 
 namespace rmx {
 
@@ -365,11 +365,12 @@ static int ensure_cap(Mlp &q, int B) {
     if (x) (void)hipFree(x);
   q.Z = q.A = q.dA = q.dZ = q.Y = nullptr;
   const size_t per = (size_t)B * q.width * q.layers * sizeof(float);
-  hipError_t e = hipMalloc(&q.Z, per);
-  if (e == hipSuccess) e = hipMalloc(&q.A, per);
-  if (e == hipSuccess) e = hipMalloc(&q.dA, (size_t)B * std::max(q.width, q.d_in) * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc(&q.dZ, (size_t)B * std::max(q.width, q.d_in) * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc(&q.Y, (size_t)B * sizeof(float));
+  hipError_t e = device_malloc((void **)&q.Z, per);
+  if (e == hipSuccess) e = device_malloc((void **)&q.A, per);
+  const size_t one = (size_t)B * std::max(q.width, q.d_in) * sizeof(float);
+  if (e == hipSuccess) e = device_malloc((void **)&q.dA, one);
+  if (e == hipSuccess) e = device_malloc((void **)&q.dZ, one);
+  if (e == hipSuccess) e = device_malloc((void **)&q.Y, (size_t)B * sizeof(float));
   if (e != hipSuccess) return RM_ERR_NOMEM;
   q.cap_b = B;
   return RM_OK;
@@ -484,7 +485,7 @@ int rm_mlp_create(int32_t d_in, int32_t width, int32_t n_layers, int32_t prec,
   }
   hipError_t e = hipSuccess;
   for (float **x : {&q->p, &q->g, &q->m, &q->v})
-    if (e == hipSuccess) e = hipMalloc(x, (size_t)off * sizeof(float));
+    if (e == hipSuccess) e = device_malloc((void **)x, (size_t)off * sizeof(float));
   if (e == hipSuccess) e = hipMemcpy(q->p, h.data(), (size_t)off * sizeof(float), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemset(q->g, 0, (size_t)off * sizeof(float));
   if (e == hipSuccess) e = hipMemset(q->m, 0, (size_t)off * sizeof(float));
@@ -580,7 +581,7 @@ int rm_mesh_from_density(const float *dens, int32_t nw, double lo, double hi,
     return (set_error(RM_ERR_ARG, "bad mesh arguments"), RM_ERR_ARG);
   hipStream_t st = (hipStream_t)stream;
   double *cum = nullptr;
-  if (hipMallocAsync((void **)&cum, (size_t)(nw + 1) * sizeof(double), st) !=
+  if (stream_malloc((void **)&cum, (size_t)(nw + 1) * sizeof(double), st) !=
       hipSuccess)
     return (set_error(RM_ERR_NOMEM, "cdf buffer"), RM_ERR_NOMEM);
   hipLaunchKernelGGL(density_cdf_kernel, dim3(1), dim3(256), 0, st, dens, nw,

@@ -577,7 +577,7 @@ int rm_convolve_gaussian(const double *E, int64_t M, const double *omega_in,
   const double r = 0.5 / (s * s);
   char *ws = nullptr;
   const size_t bytes = (size_t)M * (sizeof(double) + 2 * sizeof(int64_t));
-  hipError_t e = hipMallocAsync((void **)&ws, bytes, st);
+  hipError_t e = stream_malloc((void **)&ws, bytes, st);
   if (e != hipSuccess) return pp_hip(fn, e);
   double *dE = (double *)ws;
   int64_t *lo = (int64_t *)(dE + M);
@@ -642,7 +642,7 @@ int rm_effective_collision_strengths(const double *E, int64_t M,
       ((size_t)n_target + nT + std::max<size_t>(1, (size_t)M * nT) +
        (size_t)n_part * P * nT);
   char *ws = nullptr;
-  hipError_t e = hipMallocAsync((void **)&ws, bytes, st);
+  hipError_t e = stream_malloc((void **)&ws, bytes, st);
   if (e != hipSuccess) return pp_hip(fn, e);
   double *d_lev = (double *)ws;
   double *d_kT = d_lev + n_target;
@@ -717,7 +717,7 @@ int rm_group_collision_strengths(const double *omega, int64_t M,
   }
   hipStream_t st = (hipStream_t)stream;
   int32_t *d_tab = nullptr;
-  hipError_t e = hipMallocAsync((void **)&d_tab, tab.size() * sizeof(int32_t), st);
+  hipError_t e = stream_malloc((void **)&d_tab, tab.size() * sizeof(int32_t), st);
   if (e != hipSuccess) return pp_hip(fn, e);
   e = hipMemcpyAsync(d_tab, tab.data(), tab.size() * sizeof(int32_t),
                      hipMemcpyHostToDevice, st);

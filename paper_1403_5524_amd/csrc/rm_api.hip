@@ -277,9 +277,10 @@ static int check_opts(const rm_opts *o, rm_opts *out, bool photo = false) {
 // of this library's own, one per device, that keeps up to kPoolKeep bytes
 // between calls: the device's default pool gives everything back at the next
 // synchronisation, and mapping it again took longer than the kernels of an
-// ordinary call (K matrices of 60 channels 14.5 ms, 3.4 of them kernels).
+// ordinary call (K matrices of 117 channels 14.5 ms, 3.4 of them kernels).
 // The pool's idle memory is given back when the last symmetry handle of the
-// device is freed, and before an allocation of this library is given up.
+// device is freed, and before an allocation of this library is given up: every
+// one goes through pool_alloc, stream_malloc or device_malloc.
 // Blocks are handed from stream to stream by the runtime, in stream order.
 constexpr uint64_t kPoolKeep = 16ull << 30;
 struct DevicePool {
@@ -311,34 +312,41 @@ static hipError_t device_pool(hipMemPool_t *out) {
   return hipSuccess;
 }
 
-// Give the pool's idle memory back (st: a stream whose frees may be pending).
-static void pool_trim(hipStream_t st) {
+// Give the pool's idle memory back, what frees still under way on any stream
+// leave idle included.
+static void pool_trim() {
   hipMemPool_t pool;
-  if (hipStreamSynchronize(st) != hipSuccess) return;
-  if (device_pool(&pool) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+  if (hipDeviceSynchronize() == hipSuccess && device_pool(&pool) == hipSuccess)
+    (void)hipMemPoolTrimTo(pool, 0);
 }
 
-static hipError_t pool_alloc(void **p, size_t bytes, hipStream_t st) {
-  hipMemPool_t pool;
-  hipError_t e = device_pool(&pool);
-  if (e == hipSuccess) e = hipMallocFromPoolAsync(p, bytes, pool, st);
+// alloc(), once more without the pool's idle memory if memory ran out.  A
+// failure is returned and not left behind for the next call to report.
+template <class ALLOC>
+static hipError_t alloc_or_trim(ALLOC alloc) {
+  hipError_t e = alloc();
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
-    pool_trim(st);
-    e = hipMallocFromPoolAsync(p, bytes, pool, st);
+    pool_trim();
+    e = alloc();
   }
+  if (e != hipSuccess) (void)hipGetLastError();
   return e;
 }
 
-// hipMalloc that does not fail for what the pool holds.
-static hipError_t device_malloc(void **p, size_t bytes) {
-  hipError_t e = hipMalloc(p, bytes);
-  if (e == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
-    pool_trim(nullptr);
-    e = hipMalloc(p, bytes);
-  }
-  return e;
+hipError_t pool_alloc(void **p, size_t bytes, hipStream_t st) {
+  hipMemPool_t pool;
+  const hipError_t e = device_pool(&pool);
+  if (e != hipSuccess) return e;
+  return alloc_or_trim([&] { return hipMallocFromPoolAsync(p, bytes, pool, st); });
+}
+
+hipError_t stream_malloc(void **p, size_t bytes, hipStream_t st) {
+  return alloc_or_trim([&] { return hipMallocAsync(p, bytes, st); });
+}
+
+hipError_t device_malloc(void **p, size_t bytes) {
+  return alloc_or_trim([&] { return hipMalloc(p, bytes); });
 }
 
 // A symmetry handle of device `dev` appears (+1) or goes (-1).

@@ -161,6 +161,12 @@ struct PsOut {
   int ld_mult;
 };
 
+// hipMallocFromPoolAsync from the library's own pool, hipMallocAsync and
+// hipMalloc; none of them fails for memory that the pool holds idle.
+hipError_t pool_alloc(void **p, size_t bytes, hipStream_t st);
+hipError_t stream_malloc(void **p, size_t bytes, hipStream_t st);
+hipError_t device_malloc(void **p, size_t bytes);
+
 // Tile variants of the pole-sum kernels (chosen by the autotuner).
 enum PsVariant {
   PS_F64_T32_E16 = 0,   // FP64, 32x32 tile pairs, 16 energies per WG
