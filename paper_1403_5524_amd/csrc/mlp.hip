@@ -364,6 +364,7 @@ static int ensure_cap(Mlp &q, int B) {
   for (float *x : {q.Z, q.A, q.dA, q.dZ, q.Y})
     if (x) (void)hipFree(x);
   q.Z = q.A = q.dA = q.dZ = q.Y = nullptr;
+  q.cap_b = 0;  // until they are there again
   const size_t per = (size_t)B * q.width * q.layers * sizeof(float);
   hipError_t e = device_malloc((void **)&q.Z, per);
   if (e == hipSuccess) e = device_malloc((void **)&q.A, per);

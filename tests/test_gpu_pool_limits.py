@@ -57,3 +57,19 @@ def test_kept_memory_does_not_stand_in_the_way(call):
         fill.clear()
         torch.cuda.empty_cache()
         h.free()
+
+
+def test_network_after_a_batch_that_does_not_fit():
+    """The activations of 2^31 - 1 samples (70 TB) are refused, and the network
+    still serves the batches it served before."""
+    import torch
+    from paper_1403_5524_amd import native
+    m = native.Mlp(1, 4096, 2)
+    X = torch.linspace(-1, 1, 8, device="cuda:0")[:, None].contiguous()
+    Y = m.forward(X).cpu()
+    with pytest.raises(native.RmError) as ei:
+        m.forward(torch.empty((2 ** 31 - 1, 1), device="cuda:0"))
+    assert ei.value.code == native.RM_ERR_NOMEM
+    assert torch.equal(m.forward(X).cpu(), Y)
+    m.free()
+    torch.cuda.empty_cache()
