@@ -21,8 +21,13 @@
  * functions; device pointers must address memory of the current HIP device,
  * and `stream` is a hipStream_t (NULL = the null stream).  Work is enqueued
  * on `stream` and the call returns without synchronising, except where
- * stated.  No function throws; each returns an rm_status code and, when it is
- * not RM_OK, rm_last_error() describes the failure (thread-local).
+ * stated: arrays that it reads or writes must live until that work is done,
+ * and another stream must be made to wait before it reads the results.  (A
+ * handle may be changed or freed while calls that use it are under way: rm_free,
+ * rm_set_propagation, rm_load_dipoles and rm_load_widths wait for the whole
+ * device, and what rm_set_gailitis changes is read before a call returns.)
+ * No function throws; each returns an rm_status code and, when it is not
+ * RM_OK, rm_last_error() describes the failure (thread-local).
  *
  * Argument validation happens before anything is enqueued: an RM_ERR_ARG
  * return has touched no device memory.
@@ -346,7 +351,7 @@ int rm_mesh_from_density(const float *dens, int32_t nw, double lo, double hi,
  * device, R(A) matched to Coulomb / Whittaker functions at r = A (terms
  * beyond A dropped).  n_sec = 0 switches the propagation off.  rm_rmatrix
  * still returns R(a); rm_photoionization rejects propagated symmetries.
- * Synchronises `stream`.  Errors: RM_ERR_ARG (n_sec outside [0, 1e5], lmax
+ * Synchronises the device.  Errors: RM_ERR_ARG (n_sec outside [0, 1e5], lmax
  * outside [0, 8], A not finite or <= a, beta null, not finite or not
  * symmetric), RM_ERR_STATE, RM_ERR_NOMEM, RM_ERR_HIP. */
 int rm_set_propagation(rm_sym_t sym, double A, int32_t n_sec, int32_t lmax,
@@ -396,14 +401,14 @@ int rm_set_gailitis(rm_sym_t sym, int32_t max_terms, void *stream);
  *
  * rm_load_dipoles: attach d (host [n_poles], finite, input pole order) to a
  * loaded symmetry (copied to its device; replaces an earlier vector after
- * synchronising `stream`).  Errors: RM_ERR_ARG, RM_ERR_STATE, RM_ERR_NOMEM,
+ * synchronising the device).  Errors: RM_ERR_ARG, RM_ERR_STATE, RM_ERR_NOMEM,
  * RM_ERR_HIP. */
 int rm_load_dipoles(rm_sym_t sym, const double *d, void *stream);
 
 /* rm_load_widths: attach the radiative widths Gamma_k (host [n_poles], finite,
  * >= 0, Ry, input pole order) of the inner-region states to a loaded
  * symmetry, for the damped photoionization (replaces earlier widths after
- * synchronising `stream`).  Errors: RM_ERR_ARG, RM_ERR_STATE, RM_ERR_NOMEM,
+ * synchronising the device).  Errors: RM_ERR_ARG, RM_ERR_STATE, RM_ERR_NOMEM,
  * RM_ERR_HIP.
  *
  * Radiation damping (the damped photoionization module of Sec. 3, Tables

@@ -1508,8 +1508,8 @@ int rm_set_propagation(rm_sym_t sym, double A, int32_t n_sec, int32_t lmax,
   if (rc) return rc;
   if (n_sec < 0 || n_sec > 100000) return fail(RM_ERR_ARG, "n_sec outside [0, 1e5]");
   if (lmax < 0 || lmax > 8) return fail(RM_ERR_ARG, "lmax outside [0, 8]");
-  hipStream_t st = (hipStream_t)stream;
-  RM_HIP(hipStreamSynchronize(st));  // queued sweeps may still read the old sectors
+  // sweeps queued on any stream may still read the old sectors
+  RM_HIP(hipDeviceSynchronize());
   if (n_sec == 0) {
     sym->n_sec = 0;
     sym->gl_terms = 0;
@@ -1678,7 +1678,7 @@ int rm_set_gailitis(rm_sym_t sym, int32_t max_terms, void *stream) {
   if (max_terms > 0 && sym->n_sec == 0)
     return fail(RM_ERR_STATE, "the asymptotic expansion needs the propagation "
                               "(rm_set_propagation) first");
-  RM_HIP(hipStreamSynchronize((hipStream_t)stream));  // queued sweeps read it
+  RM_HIP(hipStreamSynchronize((hipStream_t)stream));
   sym->gl_terms = max_terms;
   return RM_OK;
 }
@@ -1692,9 +1692,8 @@ int rm_load_dipoles(rm_sym_t sym, const double *d, void *stream) {
     if (!std::isfinite(d[k])) return fail(RM_ERR_ARG, "dipole %d not finite", k);
     h[k] = d[k];
   }
-  hipStream_t st = (hipStream_t)stream;
-  // kernels already queued may still read the old vector
-  RM_HIP(hipStreamSynchronize(st));
+  // kernels already queued, on any stream, may still read the old vector
+  RM_HIP(hipDeviceSynchronize());
   if (!sym->dip) RM_HIP(device_malloc((void **)&sym->dip, h.size() * sizeof(double)));
   RM_HIP(hipMemcpy(sym->dip, h.data(), h.size() * sizeof(double),
                    hipMemcpyHostToDevice));
@@ -1711,8 +1710,8 @@ int rm_load_widths(rm_sym_t sym, const double *gamma, void *stream) {
       return fail(RM_ERR_ARG, "width %d not finite and >= 0", k);
     h[k] = gamma[k];
   }
-  hipStream_t st = (hipStream_t)stream;
-  RM_HIP(hipStreamSynchronize(st));  // queued kernels may read the old ones
+  // kernels already queued, on any stream, may still read the old ones
+  RM_HIP(hipDeviceSynchronize());
   if (!sym->gam) RM_HIP(device_malloc((void **)&sym->gam, h.size() * sizeof(double)));
   RM_HIP(hipMemcpy(sym->gam, h.data(), h.size() * sizeof(double),
                    hipMemcpyHostToDevice));

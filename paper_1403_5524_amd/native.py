@@ -190,9 +190,16 @@ def _f32(t, numel=None, name="tensor", optional=False):
     return _dev(t, torch.float32, numel, name, optional)
 
 
-def _stream():
+def _stream(*used):
+    """The current stream.  ``used``: tensors that work still under way when the
+    call returns reads or writes; one that belongs to another stream keeps its
+    memory until that work is done, though the caller lets go of it before."""
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    st = torch.cuda.current_stream()
+    for t in used:
+        if t is not None:
+            t.record_stream(st)
+    return ctypes.c_void_p(st.cuda_stream)
 
 
 def make_opts(prec=RM_PREC_FP64, near_delta=0.0, solve_fp32=0, refine_iters=0,
@@ -267,7 +274,8 @@ def rm_sweep_energies(syms, n_target, E, opts=None, omega=None, status=None):
     arr = (ctypes.c_void_p * len(syms))(*[s.handle for s in syms])
     o = opts if opts is not None else make_opts()
     _check(lib().rm_sweep_energies(arr, len(syms), n_target, pE, M,
-                                   ctypes.byref(o), po, ps, _stream()))
+                                   ctypes.byref(o), po, ps,
+                                   _stream(E, omega, status)))
     return omega, status
 
 
@@ -299,7 +307,7 @@ def rm_kmatrix(sym, E, opts=None, want_R=False):
         if want_R else None
     o = opts if opts is not None else make_opts()
     _check(lib().rm_kmatrix(sym.handle, pE, m, ctypes.byref(o), _ptr(K),
-                            _ptr(no), _ptr(R), _ptr(st), _stream()))
+                            _ptr(no), _ptr(R), _ptr(st), _stream(E)))
     return K, no, R, st
 
 
@@ -323,7 +331,7 @@ def rm_rmatrix(sym, E, opts=None):
     R = torch.empty((m, n, n), dtype=torch.float64, device=E.device)
     o = opts if opts is not None else make_opts()
     _check(lib().rm_rmatrix(sym.handle, pE, m, ctypes.byref(o), _ptr(R),
-                            _stream()))
+                            _stream(E)))
     return R
 
 
@@ -562,7 +570,8 @@ def rm_photoionization(syms, E, e0, opts=None, sigma=None, status=None):
     arr = (ctypes.c_void_p * len(syms))(*[s.handle for s in syms])
     o = opts if opts is not None else make_opts()
     _check(lib().rm_photoionization(arr, len(syms), pE, M, float(e0),
-                                    ctypes.byref(o), psg, pst, _stream()))
+                                    ctypes.byref(o), psg, pst,
+                                    _stream(E, sigma, status)))
     return sigma, status
 
 
