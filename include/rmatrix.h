@@ -138,8 +138,10 @@ typedef struct {
 } rm_opts;
 
 /* rm_opts.flags: time the pole-sum tile variants on the first plan of each
- * (channels, poles, precision) and keep the fastest (in memory, and in the
- * file named by the environment variable RM_TUNE_CACHE when set). */
+ * (channels, poles, precision) and, in FP64, each class of mesh (how much of
+ * its pole sum is interpolated over groups of energies), and keep the fastest
+ * (in memory, and in the file named by the environment variable RM_TUNE_CACHE
+ * when set). */
 #define RM_FLAG_AUTOTUNE 0x1u
 /* rm_opts.flags: the pole sum has two forms.  The scaled-W kernels
  * contract (W diag(d)) W^T per energy tile and need nothing beyond W.  The

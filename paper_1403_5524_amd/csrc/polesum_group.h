@@ -25,6 +25,12 @@ struct PgGroup {
   double cen, h; // centre and half width
 };
 
+// Energies times chunks of poles of an interpolated group, nc chunks in all.
+__device__ __forceinline__ int64_t pg_work(const PgGroup &p, int nc) {
+  const int nn = p.kb - p.ka;
+  return (int64_t)PG_NODE * (nc - nn) + (int64_t)p.cnt * nn;
+}
+
 // Group grp of the launch's chunk (groups are cut on the whole mesh, so the
 // chunk may begin or end inside one), for a workgroup of 256.
 __device__ __forceinline__ PgGroup pg_decide(const PsLaunch &L, const SymDev &S,
@@ -85,9 +91,7 @@ __device__ __forceinline__ PgGroup pg_decide(const PsLaunch &L, const SymDev &S,
       (sm.redi[0][2] | sm.redi[1][2]) == 0 && p.h > 0.0 ? 1 : 0);
   // The far phase costs 16 energies' worth of the far chunks; required to
   // take a quarter off, since the direct sum has eight times the workgroups.
-  const int nn = p.kb - p.ka;
-  p.interp = fine && (int64_t)4 * (PG_NODE * (nc - nn) + p.cnt * nn) <
-                         (int64_t)3 * p.cnt * nc;
+  p.interp = fine && 4 * pg_work(p, nc) < (int64_t)3 * p.cnt * nc;
   return p;
 }
 

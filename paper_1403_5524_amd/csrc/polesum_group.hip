@@ -251,6 +251,29 @@ void polesum_group_kernel(PsLaunch L) {
   }
 }
 
+__global__ __launch_bounds__(256) void group_work_kernel(PsLaunch L,
+                                                         int64_t *work) {
+  __shared__ PgDecide dec;
+  const PgGroup P = pg_decide(L, L.syms[0], blockIdx.x, dec);
+  if (threadIdx.x != 0) return;
+  const int nc = L.syms[0].nh_pad / PG_KC;
+  const int64_t direct = (int64_t)P.cnt * nc;
+  work[2 * blockIdx.x] = P.interp ? pg_work(P, nc) : direct;
+  work[2 * blockIdx.x + 1] = direct;
+}
+
+hipError_t launch_group_work(const SymDev *sym, const double *E, int64_t m,
+                             int ngrp, int64_t *work, hipStream_t st) {
+  PsLaunch L{};
+  L.syms = sym;
+  L.E = E;
+  L.m = (int)m;
+  L.m_all = m;
+  hipLaunchKernelGGL(group_work_kernel, dim3((unsigned)ngrp), dim3(256), 0, st, L,
+                     work);
+  return hipGetLastError();
+}
+
 hipError_t launch_polesum_group(const PsLaunch &L, hipStream_t st) {
   const dim3 grid((unsigned)(8 * ((4 * L.n_items + 7) / 8)));
   if (L.part == 1)

@@ -548,14 +548,16 @@ static void plan_free_device(Plan &p) {
   p.chan = nullptr;
 }
 
-// ---- autotuner: fastest mixed tile variant per (n, N_H, precision)
+// ---- autotuner: fastest tile variant per (n, N_H, precision, mesh class)
 
 struct TuneKey {
   int n, nh, prec;
+  int mesh;  // FP64: f64_mesh_class; 0 for the mixed precisions
   bool operator<(const TuneKey &o) const {
-    return std::tie(n, nh, prec) < std::tie(o.n, o.nh, o.prec);
+    return std::tie(n, nh, prec, mesh) < std::tie(o.n, o.nh, o.prec, o.mesh);
   }
 };
+constexpr int kMeshClasses = 4;
 static std::map<TuneKey, int> g_tuned;
 static std::mutex g_tune_mu;
 static bool g_tune_loaded = false;
@@ -569,17 +571,23 @@ static void tune_load() {
   if (!path) return;
   FILE *f = std::fopen(path, "r");
   if (!f) return;
-  int n, nh, prec, v;
-  while (std::fscanf(f, "%d %d %d %d", &n, &nh, &prec, &v) == 4) {
+  // a line: channels, poles, precision, variant and, for FP64, mesh class
+  char line[256];
+  while (std::fgets(line, sizeof line, f)) {
+    int n, nh, prec, v, mesh = 0;
+    const int k = std::sscanf(line, "%d %d %d %d %d", &n, &nh, &prec, &v, &mesh);
+    if (k < 4) continue;
     // an entry counts only if its variant belongs to its precision: an FP64
     // kernel launched for a mixed sweep (or the reverse) would read staged
-    // operands the sweep never formed
-    const bool ok64 = prec == RM_PREC_FP64 &&
+    // operands the sweep never formed; an FP64 entry without a mesh class was
+    // timed on one mesh and says nothing of others
+    const bool ok64 = prec == RM_PREC_FP64 && k == 5 && mesh >= 0 &&
+                      mesh < kMeshClasses &&
                       (v == PS_F64_T32_E16 || v == PS_PD64);
-    const bool okmx = (prec == RM_PREC_FP32 || prec == RM_PREC_BF16X3) &&
+    const bool okmx = (prec == RM_PREC_FP32 || prec == RM_PREC_BF16X3) && k == 4 &&
                       (v == PS_MX_J16_E8 || v == PS_MX_J8_E8 ||
                        v == PS_MX_J16_E4 || v == PS_PD);
-    if (n > 0 && nh > 0 && (ok64 || okmx)) g_tuned[{n, nh, prec}] = v;
+    if (n > 0 && nh > 0 && (ok64 || okmx)) g_tuned[{n, nh, prec, mesh}] = v;
   }
   std::fclose(f);
 }
@@ -589,9 +597,12 @@ static void tune_store() {
   if (!path) return;
   FILE *f = std::fopen(path, "w");
   if (!f) return;
-  for (auto &kv : g_tuned)
-    std::fprintf(f, "%d %d %d %d\n", kv.first.n, kv.first.nh, kv.first.prec,
-                 kv.second);
+  for (auto &kv : g_tuned) {
+    const TuneKey &t = kv.first;
+    std::fprintf(f, "%d %d %d %d", t.n, t.nh, t.prec, kv.second);
+    if (t.prec == RM_PREC_FP64) std::fprintf(f, " %d", t.mesh);
+    std::fprintf(f, "\n");
+  }
   std::fclose(f);
 }
 
@@ -660,6 +671,44 @@ static bool ensure_pd(Sym &s, int prec, hipStream_t st) {
 static void build_items(const Plan &p, int variant, int64_t m,
                         std::vector<PsItem> &out);
 
+constexpr int64_t kTuneEnergies = 512;
+
+// What the FP64 scaled-W sum of these energies costs beside a direct sum, which
+// is what the pair form has to be compared with: 0 more than three quarters (no
+// group of energies interpolates), then by halves, 3 below 3/16.  One choice
+// for all meshes would keep what was fastest on the first one: at 200 channels
+// and 8000 poles the sum takes 27 ms on coarse meshes and 5.2 on fine ones.
+// Synchronises `st`.
+static int f64_mesh_class(const Sym &s, const double *E, int64_t m,
+                          hipStream_t st, int *cls) {
+  *cls = 0;
+  const int64_t mt = std::min<int64_t>(m, kTuneEnergies);
+  if (ps_f64_variant(PS_F64_T32_E16, s.nh, mt) != PS_F64_GROUP) return RM_OK;
+  constexpr int kGroups = 8;
+  static_assert(kTuneEnergies <= 64 * kGroups, "a work entry per group");
+  int64_t work[kGroups][2];
+  const int ngrp = ps_groups(PS_F64_GROUP, mt, true);
+  DevBuf buf;
+  int rc = dev_alloc(buf, sizeof(SymDev) + sizeof work, st);
+  if (rc) return rc;
+  const SymDev sd = s.dev();
+  int64_t *d_work = (int64_t *)buf.p;
+  SymDev *d_sym = (SymDev *)((char *)buf.p + sizeof work);
+  RM_HIP(hipMemcpyAsync(d_sym, &sd, sizeof sd, hipMemcpyHostToDevice, st));
+  RM_HIP(launch_group_work(d_sym, E, mt, ngrp, d_work, st));
+  RM_HIP(hipMemcpyAsync(work, d_work, sizeof work[0] * ngrp,
+                        hipMemcpyDeviceToHost, st));
+  RM_HIP(hipStreamSynchronize(st));
+  int64_t part = 0, all = 0;
+  for (int g = 0; g < ngrp; ++g) {
+    part += work[g][0];
+    all += work[g][1];
+  }
+  for (int64_t lim = 4 * part; *cls + 1 < kMeshClasses && lim <= 3 * all; lim *= 2)
+    ++*cls;
+  return RM_OK;
+}
+
 // Time every mixed variant on up to 512 energies of E (device) and keep the
 // fastest.  Synchronises `st`.
 static int tune_variants(const Sym &s, int prec, double delta, double band,
@@ -683,7 +732,7 @@ static int tune_f64(const Sym &s, const double *E, int64_t m, hipStream_t st,
 static int tune_variants(const Sym &s, int prec, double delta, double band,
                          const double *E, int64_t m, hipStream_t st,
                          const std::vector<int> &cands, int *chosen) {
-  const int64_t mt = std::min<int64_t>(m, 512);
+  const int64_t mt = std::min<int64_t>(m, kTuneEnergies);
   const int64_t nn = (int64_t)s.n * s.n;
   double *R = nullptr;
   SymDev *dsym = nullptr;
@@ -771,15 +820,18 @@ static int pick_variant(Sym &s, const rm_opts &o, const double *E, int64_t M,
       return RM_OK;
     }
     if (!(o.flags & RM_FLAG_AUTOTUNE) || M <= 0) return RM_OK;
-    auto it = g_tuned.find({s.n, s.nh, o.prec});
+    int mesh = 0;
+    int rc = f64_mesh_class(s, E, M, st, &mesh);
+    if (rc) return rc;
+    auto it = g_tuned.find({s.n, s.nh, o.prec, mesh});
     if (it != g_tuned.end()) {
       if (it->second == PS_F64_T32_E16 || ensure_pd(s, o.prec, st)) *v = it->second;
       return RM_OK;
     }
     if (!ensure_pd(s, o.prec, st)) return RM_OK;
-    int rc = tune_f64(s, E, M, st, v);
+    rc = tune_f64(s, E, M, st, v);
     if (rc) return rc;
-    g_tuned[{s.n, s.nh, o.prec}] = *v;
+    g_tuned[{s.n, s.nh, o.prec, mesh}] = *v;
     tune_store();
     return RM_OK;
   }
@@ -788,7 +840,7 @@ static int pick_variant(Sym &s, const rm_opts &o, const double *E, int64_t M,
     *v = PS_PD;
     return RM_OK;
   }
-  auto it = g_tuned.find({s.n, s.nh, o.prec});
+  auto it = g_tuned.find({s.n, s.nh, o.prec, 0});
   if (it != g_tuned.end() && (pd || it->second != PS_PD)) {
     *v = it->second;
     return RM_OK;
@@ -799,7 +851,7 @@ static int pick_variant(Sym &s, const rm_opts &o, const double *E, int64_t M,
   }
   int rc = tune_sym(s, o.prec, o.near_delta, o.band_delta, E, M, st, pd, v);
   if (rc) return rc;
-  if (pd) g_tuned[{s.n, s.nh, o.prec}] = *v;  // a table without the pair
+  if (pd) g_tuned[{s.n, s.nh, o.prec, 0}] = *v;  // a table without the pair
   tune_store();                               // form is not cached
   return RM_OK;
 }

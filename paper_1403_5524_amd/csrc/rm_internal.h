@@ -213,6 +213,10 @@ hipError_t launch_polesum(const PsLaunch &L, int variant, hipStream_t st);
 hipError_t launch_polesum_pd(const PsLaunch &L, hipStream_t st);
 hipError_t launch_polesum_pd64(const PsLaunch &L, hipStream_t st);
 hipError_t launch_polesum_group(const PsLaunch &L, hipStream_t st);
+// Chunks of poles that PS_F64_GROUP sums for each of the ngrp groups of a mesh
+// of m energies, and those of a direct sum: work[g][0], work[g][1] (device).
+hipError_t launch_group_work(const SymDev *sym, const double *E, int64_t m,
+                             int ngrp, int64_t *work, hipStream_t st);
 // The FP64 scaled-W sum of nh poles on a mesh of m energies: in groups from
 // 64 energies and 512 poles on.  Far poles then cost 16 energies' work per
 // group (200 channels, 8000 poles, mesh step 1e-4: 0.40 ms at 64 energies
