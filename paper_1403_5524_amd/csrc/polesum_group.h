@@ -32,9 +32,13 @@ __device__ __forceinline__ int64_t pg_work(const PgGroup &p, int nc) {
 }
 
 // Group grp of the launch's chunk (groups are cut on the whole mesh, so the
-// chunk may begin or end inside one), for a workgroup of 256.
+// chunk may begin or end inside one), for a workgroup of 256.  The two kernels
+// have to come to the same decision, or a group is summed by both or by neither:
+// no product is fused with a sum here, so every step is rounded by itself and
+// the result does not depend on what the compiler makes of either kernel.
 __device__ __forceinline__ PgGroup pg_decide(const PsLaunch &L, const SymDev &S,
                                              int grp, PgDecide &sm) {
+#pragma clang fp contract(off)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   PgGroup p;
