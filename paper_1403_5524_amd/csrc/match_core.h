@@ -334,7 +334,7 @@ __device__ __forceinline__ int team_omega(const SymDev &S, int n_out, const RM_G
   n_out = uni(n_out); ldy = uni(ldy); ldq = uni(ldq); ldv = uni(ldv); no = uni(no);
   const double g2 = 2.0 * S.g;
   int nonfinite = 0;
-  if (S.ntu == S.n) {
+  if (uni(S.ntu) == uni(S.n)) {
     // one channel per level: walk the open block's lower triangle, a row of
     // it per wavefront (consecutive lanes read consecutive elements)
     for (int i = team_wave<NW>(); i < no; i += NW) {
@@ -387,7 +387,7 @@ __device__ __forceinline__ int team_omega(const SymDev &S, int n_out, const RM_G
     }
   }
   team_sync<NW>();
-  const int nt = S.ntu;
+  const int nt = uni(S.ntu);
   // W1 = G^T V (nt x no) into Qm's place, then Omega_u = W1 G (nt x nt) into V
   team_gemm<NW, 2>(Qm, ldq, as_g(S.GT), S.n, V, ldv, nt, no, no);
   team_gemm<NW, 2>(V, ldv, Qm, ldq, as_g(S.G), nt, nt, nt, no);
@@ -408,8 +408,9 @@ template <int NW>
 __device__ __forceinline__ int team_channel_functions(const SymDev &S, double Ee,
                                       RM_G ChanSlot *ch) {
   int bits = 0;
+  const int n = uni(S.n);
   const double ra = S.r_match;
-  for (int i = team_tid<NW>(); i < S.n; i += WT * NW) {
+  for (int i = team_tid<NW>(); i < n; i += WT * NW) {
     const double diff = Ee - S.e_thr[i];
     ChanSlot c;
     if (diff > 0.0) {
@@ -659,7 +660,7 @@ __global__ __launch_bounds__(WT *NW) void assemble_kernel(MatchLaunch L) {
     put_status(L, e, RM_E_NO_OPEN);
     return;
   }
-  if (S.gl_terms > 0) return;
+  if (uni(S.gl_terms) > 0) return;
   const int bits = team_channel_functions<NW>(S, Ee, P.ch);
   team_sync<NW>();
   if constexpr (DAMPED)

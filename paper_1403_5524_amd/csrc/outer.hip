@@ -22,7 +22,7 @@ __device__ __forceinline__ int team_propagate(const SymDev &S, double Ee, RM_G d
                               RM_G double *Kb, RM_G ChanSlot *ch, RM_L TeamLds<NW> &W) {
   ld = uni(ld);
   const int tid = team_tid<NW>();
-  const int n = S.n;
+  const int n = uni(S.n), n_sec = uni(S.n_sec);
   const int nsq = n * n;
   int flag = 0;
   // X = a R(a) in Aug's left half
@@ -30,14 +30,14 @@ __device__ __forceinline__ int team_propagate(const SymDev &S, double Ee, RM_G d
       n, n, [&](int i, int j) { return Aug[(int64_t)i * ld + j]; },
       [&](int i, int j, double v) { Aug[(int64_t)i * ld + j] = v * S.a; });
   team_sync<NW>();
-  for (int t = 0; t <= S.n_sec; ++t) {
+  for (int t = 0; t <= n_sec; ++t) {
     const RM_G double *O = as_g(S.prop_O + (int64_t)t * nsq);
     // Kb = O^T (X O).  X is symmetric, so inside the sectors only the tiles
     // that meet the product's lower triangle are formed and the assembly
     // below reads element (i, j) at (max, min); the final change of basis
     // forms all of it
     team_gemm_wide<NW, 2, 0, 2, 4>(Aug + n, ld, Aug, ld, O, n, n, n, n);
-    if (t == S.n_sec) {
+    if (t == n_sec) {
       team_gemm_wide<NW, 2, G_TA, 2, 4>(Kb, n, O, n, Aug + n, ld, n, n, n);
       break;
     }
@@ -152,9 +152,10 @@ __device__ __forceinline__ int team_gailitis_system(const SymDev &S, double Ee, 
                                     int no, RM_G double *gw, RM_L TeamLds<NW> &W) {
   ld = uni(ld); no = uni(no);
   const int tid = team_tid<NW>();
-  const int n = S.n, nc = n - no;
+  const int n = uni(S.n), nc = n - no;
+  const int lmax = uni(S.lmax), terms = uni(S.gl_terms);
   const double r = S.A, ir = 1.0 / S.A;
-  const int Q = gl_ring(S.lmax);
+  const int Q = gl_ring(lmax);
   constexpr int CB = kGlCols, CW = 2 * kGlCols;
   const int64_t slot = (int64_t)n * CW;
   RM_G double *ring = gw;
@@ -196,7 +197,7 @@ __device__ __forceinline__ int team_gailitis_system(const SymDev &S, double Ee, 
     bool active = real_col;
     bool ncv = false;
     double t_prev = 1.0;
-    for (int P = 1; P <= S.gl_terms; ++P) {
+    for (int P = 1; P <= terms; ++P) {
       if (!uni(wave_or(active ? 1 : 0))) break;
       RM_G double *Vn = Vs + (P & 1) * slot;
       const RM_G double *Vo = Vs + ((P - 1) & 1) * slot;
@@ -204,9 +205,9 @@ __device__ __forceinline__ int team_gailitis_system(const SymDev &S, double Ee, 
       const RM_G double *d2 = ring + gl_pos(P - 2, Q) * slot;
       RM_G double *dn = ring + gl_pos(P, Q) * slot;
       RM_G double *dd = dn + Q * slot;
-      if (S.lmax > 0)  // V(P): orders P-1 .. P-lmax are consecutive slots
-        team_gemm<NW, 2>(Vn, CW, as_g(S.gl_beta), S.lmax * n, d1, CW, n, CW,
-                     S.lmax * n);
+      if (lmax > 0)  // V(P): orders P-1 .. P-lmax are consecutive slots
+        team_gemm<NW, 2>(Vn, CW, as_g(S.gl_beta), lmax * n, d1, CW, n, CW,
+                         lmax * n);
       double tmax = 0.0;
       for (int q = tid; q < n * CB; q += WT * NW) {
         const int i = q / CB;

@@ -895,7 +895,7 @@ __device__ __forceinline__ void team_tile_stage(const RM_G T *A, int ld, int j0,
 // registers, entry q or m in lane q or m.
 template <int NW>
 __device__ __forceinline__ void team_build_moves(RM_L TeamLds<NW> &W, int j0, int cnt, int po = 0) {
-  j0 = uni(j0); cnt = uni(cnt);
+  j0 = uni(j0); cnt = uni(cnt); po = uni(po);
   team_sync<NW>();
   if (team_wave<NW>() == 0) {
     const int lane = lane_id();
