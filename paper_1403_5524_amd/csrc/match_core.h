@@ -625,17 +625,14 @@ __device__ __forceinline__ void team_assemble_damped(RM_G double *Sys,
 struct Place {
   RM_G double *work;
   RM_G ChanSlot *ch;
-  // the energy's route: a word of its own, behind the FP32 solve's n pivots in
-  // the room of n doubles at the workspace's end (the channel slots are read by
-  // the steps after the solve)
-  RM_G int *flag;
+  RM_G int *flag;  // the energy's route
 };
 __device__ inline Place place_of(const MatchLaunch &L, const SymDev &S, int sym,
                                  int e) {
   Place p;
   p.work = as_g(L.work + (int64_t)e * L.work_estride + L.work_off[sym]);
   p.ch = as_g(L.chan + (int64_t)e * L.chan_estride + L.chan_off[sym]);
-  p.flag = (RM_G int *)(p.work + (int64_t)3 * S.n * S.n + 2 * S.n) + S.n;
+  p.flag = as_g(L.route) + (int64_t)sym * L.m + e;
   return p;
 }
 
@@ -842,7 +839,8 @@ void t_kernel(MatchLaunch L) {
 // follow each other in that team (one owner of the energy's Omega row).  With
 // every slots-th energy to a slot, flagged or not, two of about twenty met at
 // 200 channels, 5.2 ms of a 29 ms sweep; with a launch per symmetry a plan of
-// eight symmetries up to 400 channels spent 20 ms here, now 12.3.
+// eight symmetries up to 400 channels spent 20 ms here, now 12.3.  The flags lie
+// together, 64 energies to two cache lines, since every team reads all of them.
 template <int NW, int NAMAX>
 __global__ __launch_bounds__(WT *NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void t_complex_kernel(MatchLaunch L) {
@@ -868,12 +866,11 @@ void t_complex_kernel(MatchLaunch L) {
           mine = 0;
 #pragma unroll 1
           for (int q = 0; q < L.n_sym; ++q) {
-            const SymDev &S = L.syms[q];
+            const RM_G int *route = as_g(L.route) + (int64_t)q * m;
 #pragma unroll
             for (int u = 0; u < FB; ++u) {
               const int f = eb + u * WT + lane_id();
-              const Place P = place_of(L, S, q, min(f, m - 1));
-              mine |= (f < m && *P.flag != 0 ? 1u : 0u) << u;
+              mine |= (f < m && route[min(f, m - 1)] != 0 ? 1u : 0u) << u;
             }
           }
           cached = FB;

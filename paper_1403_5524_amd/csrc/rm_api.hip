@@ -446,9 +446,8 @@ static int free_sym(Sym *s);
 // the whole sweep is a fixed sequence of launches: per chunk one grouped
 // pole-sum launch per tile variant and the matching's steps per symmetry.
 
-// [Aug n x 2n | K n x n | g n | v n | n]: g and v serve photoionization, the
-// last n doubles hold, as int, the n pivots of the FP32 solve's refinement and
-// behind them the energy's route
+// [Aug n x 2n | K n x n | g n | v n | pivots n]: g and v serve
+// photoionization, the pivots (as int) the FP32 solve's refinement
 static int64_t work_doubles(int n) { return match_work_doubles(n); }
 // damped photoionization: [2n x 2n real driven system, leading dimension
 // 2n + 2 | R_re n x n | R_im n x n | g_re n | g_im n]
@@ -484,6 +483,7 @@ struct Plan {
   int ext_slots = 0;
   bool want_t = true;              // the sweep forms T (set before building)
   ChanSlot *chan = nullptr;
+  int *route = nullptr;            // [symmetry][energy of the chunk]
   void *block = nullptr;           // all of the above and the tables
   bool owns_async = false;         // ... from the pool
   bool in_arena = false;           // tables and workspace in an Arena
@@ -530,6 +530,7 @@ static void plan_free_device(Plan &p) {
     p.work = nullptr;
     p.ext = nullptr;
     p.chan = nullptr;
+    p.route = nullptr;
     return;
   }
   p.sets.clear();
@@ -546,6 +547,7 @@ static void plan_free_device(Plan &p) {
   p.block = nullptr;
   p.work = nullptr;
   p.chan = nullptr;
+  p.route = nullptr;
 }
 
 // ---- autotuner: fastest tile variant per (n, N_H, precision, mesh class)
@@ -966,14 +968,18 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
   p.ext_slots = 0;
   if (!p.damped && p.want_t) {
     for (const Sym *s : v) p.ext_estride = std::max(p.ext_estride, t_ext_doubles(s->n));
-    p.ext_slots = arena ? kTExtSlotsArena : kTExtSlots;
+    const int n_max = (*std::max_element(v.begin(), v.end(), [](const Sym *x, const Sym *y) {
+                        return x->n < y->n;
+                      }))->n;
+    p.ext_slots = (int)(arena ? t_ext_slots(n_max, kTExtSlotsArena, arena->cap / 32.0)
+                              : t_ext_slots(n_max, kTExtSlots, kTExtRoom));
     while (p.ext_slots > 1 && 8.0 * p.ext_slots * (double)p.ext_estride > 16.0e9)
       p.ext_slots /= 2;
     // in an arena at most a quarter of it (none at all for very large
     // symmetries: those energies then take the route through Z)
     if (arena)
       while (p.ext_slots > 0 &&
-             (8.0 * p.ext_estride + 4.0) * p.ext_slots > 0.25 * (double)arena->cap)
+             8.0 * p.ext_estride * p.ext_slots > 0.25 * (double)arena->cap)
         p.ext_slots /= 2;
   }
   p.h_work_off = woff;
@@ -983,7 +989,7 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
     p.h_outer.push_back(q->n_sec > 0 ? 1 + (q->gl_terms > 0 ? 2 : 0) : 0);
   }
   // workspace and channel slots
-  const double per_energy = 8.0 * wacc + 32.0 * cacc;
+  const double per_energy = 8.0 * wacc + 32.0 * cacc + 4.0 * (double)v.size();
   int64_t C;
   if (arena) {
     // what the arena holds after the tables (bounded by the item tables of
@@ -991,7 +997,7 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
     const double tables = (double)sd.size() * (sizeof(SymDev) + 16) + 65536.0;
     // less the complex-system pool
     const double room = (double)arena->cap - tables -
-                        (8.0 * p.ext_estride + 4.0) * p.ext_slots - 256.0;
+                        8.0 * p.ext_estride * p.ext_slots - 256.0;
     double tiles = 0.0;
     {
       std::vector<std::pair<int, int>> tl;
@@ -1083,16 +1089,19 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
                                          : RM_ERR_HIP,
                 "plan tables: %s", hipGetErrorString(e));
   const size_t wbytes = (size_t)(C * wacc) * sizeof(double);
-  // the complex-system pool after the workspace, in one allocation
+  // no more slots than energies; the pool after the workspace, in one allocation
+  p.ext_slots = (int)std::min<int64_t>(p.ext_slots, C);
   const size_t xbytes = (size_t)(p.ext_slots * p.ext_estride) * sizeof(double);
   const size_t cbytes = (size_t)(C * cacc) * sizeof(ChanSlot);
+  const size_t rbytes = (size_t)C * v.size() * sizeof(int);
   p.owns_async = async && !arena;
   p.alloc_stream = st;
   // the complex-system pool is carved from the end of the workspace's own
   // allocation (a part per energy there timed 4 % faster at 200 channels
   // than in an allocation of its own)
   if (arena) {
-    e = arena->take(&p.work, wbytes + xbytes) && arena->take(&p.chan, cbytes)
+    e = arena->take(&p.work, wbytes + xbytes) && arena->take(&p.chan, cbytes) &&
+                arena->take(&p.route, rbytes)
             ? hipSuccess
             : hipErrorOutOfMemory;
     if (e != hipSuccess)
@@ -1100,13 +1109,15 @@ static int plan_build(Plan &p, const rm_sym_t *syms, int n_sym, int n_target,
                   "%zu-byte scratch", wbytes + xbytes + cbytes, arena->cap);
   } else {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const size_t at_chan = up(wbytes + xbytes), at_tab = at_chan + up(cbytes);
+    const size_t at_chan = up(wbytes + xbytes), at_route = at_chan + up(cbytes);
+    const size_t at_tab = at_route + up(rbytes);
     e = async ? pool_alloc(&p.block, at_tab + blob.size(), st)
               : device_malloc(&p.block, at_tab + blob.size());
     if (e == hipSuccess) {
       char *base = (char *)p.block;
       p.work = (double *)base;
       p.chan = (ChanSlot *)(base + at_chan);
+      p.route = (int *)(base + at_route);
       for (auto &x : pieces) *x.first = base + at_tab + x.second;
       e = hipMemcpyAsync(base + at_tab, blob.data(), blob.size(),
                          hipMemcpyHostToDevice, st);
@@ -1197,6 +1208,7 @@ static int plan_enqueue(Plan &p, hipStream_t st) {
     L.ext = p.ext;
     L.ext_estride = p.ext_estride;
     L.ext_slots = p.ext_slots;
+    L.route = p.route;
     L.chan = p.chan;
     L.chan_estride = p.chan_estride;
     L.chan_off = p.d_chan_off;
@@ -1858,12 +1870,13 @@ int rm_collision_strengths(rm_sym_t sym, const double *K, const int32_t *n_open,
   const Sym &s = *sym;
   const int64_t ws = work_doubles(s.n), xs = t_ext_doubles(s.n);
   const int64_t C = std::max<int64_t>(1, std::min<int64_t>(m, (int64_t)(8.0e9 / (8.0 * ws))));
-  int slots = kTExtSlots;
+  int64_t slots = std::min(C, t_ext_slots(s.n, kTExtSlots, kTExtRoom));
   while (slots > 1 && 8.0 * slots * (double)xs > 16.0e9) slots /= 2;
-  DevBuf work, tabs, chan, ext;
+  DevBuf work, tabs, chan, ext, route;
   if ((rc = dev_alloc(work, (size_t)(C * ws) * sizeof(double), st))) return rc;
   if ((rc = dev_alloc(ext, (size_t)(slots * xs) * sizeof(double), st))) return rc;
   if ((rc = dev_alloc(chan, (size_t)(C * s.n) * sizeof(ChanSlot), st))) return rc;
+  if ((rc = dev_alloc(route, (size_t)C * sizeof(int), st))) return rc;
   if ((rc = dev_alloc(tabs, sizeof(SymDev) + sizeof(int64_t), st))) return rc;
   const SymDev sd = s.dev();
   const int64_t zero = 0;
@@ -1883,7 +1896,8 @@ int rm_collision_strengths(rm_sym_t sym, const double *K, const int32_t *n_open,
     L.work_estride = ws;
     L.ext = (double *)ext.p;
     L.ext_estride = xs;
-    L.ext_slots = slots;
+    L.ext_slots = (int)slots;
+    L.route = (int *)route.p;
     L.h_n = &s.n;
     L.work_off = (const int64_t *)((char *)tabs.p + sizeof(SymDev));
     L.chan = (ChanSlot *)chan.p;           // rank table of the K input

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <algorithm>
 #include <utility>
 #include <vector>
 
@@ -20,11 +22,22 @@ constexpr double kPadPole = 1.0e30;  // padding poles sit far from any energy
 // energies, so its buffers form a small pool: the team of slot q takes every
 // q-th, (q + slots)-th, ... energy of the chunk that needs the route.  Without
 // a pool those energies take the route through Z = L^-1 K instead.
-constexpr int kTExtSlots = 64;   // pool slots of an allocating sweep
-constexpr int kTExtSlotsArena = 16;  // of a sweep that may not allocate
 __host__ __device__ inline int64_t t_ext_doubles(int n) {
   return (int64_t)6 * n * n;
 }
+// Slots of symmetries of up to n channels: `least` of them, more while they take
+// no more than `room` bytes together, up to the teams that are resident at once.
+// At a tenth of the energies and more the slots are what the chunk waits for
+// (20 channels, all of 8192 energies: 13.7 ms with 64 slots, 1.4 with 1024;
+// 200 channels, a tenth of 2048: 16.5 ms with 64, 11.3 with 133).
+inline int64_t t_ext_slots(int n, int64_t least, double room) {
+  const int64_t resident = n <= 32 ? 1024 : n <= 128 ? 512 : 256;
+  const int64_t fit = (int64_t)(room / (8.0 * (double)t_ext_doubles(n)));
+  return std::min(resident, std::max(least, fit));
+}
+constexpr int kTExtSlots = 64;       // at least, of an allocating sweep ...
+constexpr double kTExtRoom = 256e6;  // ... and more within this
+constexpr int kTExtSlotsArena = 16;  // at least, of a sweep that may not allocate
 
 // The asymptotic expansion beyond A works on blocks of kGlCols open
 // channels; its per-energy scratch (after the symmetry's workspace) holds a
@@ -261,6 +274,7 @@ struct MatchLaunch {
   double *work;               // [M | B] (n x 2n), K (n x n), 2n, n pivots
   int64_t work_estride;
   const int64_t *work_off;    // device [n_sym]
+  int *route;                 // device [n_sym][m]: an energy's way (below)
   ChanSlot *chan;
   int64_t chan_estride;
   const int64_t *chan_off;    // device [n_sym]
@@ -278,6 +292,9 @@ struct MatchLaunch {
   // 2n x 2n real form of the complex driven system (leading dimension
   // 2n + 2), then R_re, R_im (n x n each) and g_re, g_im (n each)
   int damped;
+  // route: 1 where a step leaves an energy to a later one, which reads it: the
+  // FP32 solve to the FP64 factorisation, then the T step to the routes for
+  // large K
   // the T step's complex-system pool (nullable): ext_slots slots of
   // ext_estride doubles (at least t_ext_doubles(n) of every symmetry) at
   // ext + slot * ext_estride
