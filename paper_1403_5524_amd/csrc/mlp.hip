@@ -5,7 +5,7 @@
 // log-density of mesh points.  Layers are dense, width W, SiLU activations
 // (x sigma(x)) between them and a linear output.  Matrix products run on the
 // gfx950 matrix cores with BF16 operands (weights and activations rounded to
-// BF16 when staged in LDS) and FP32 accumulation (v_mfma_f32_16x16x32_bf16);
+// BF16 as they enter a product) and FP32 accumulation (v_mfma_f32_16x16x32_bf16);
 // a debug precision runs the same kernels with FP32 operands
 // (v_mfma_f32_16x16x4f32).  Master weights, gradients and Adam moments are
 // FP32.  Parameters are one flat FP32 array: per layer W_l [out][in] then
@@ -79,22 +79,24 @@ __device__ __forceinline__ void mlp_load(float (&x)[8], const float *X, int ld,
 // gradient, one thread per column, 178 us; a step of 16 -> 256 -> 256 -> 256
 // -> 1 with 1024 samples took 1280 us and takes 74 us.
 //
-// A wavefront holds 16 F x 16 F of the result.  Forward and backward: 2 x 2
-// wavefronts, each summing all of K in steps of 32 in ascending order.
+// A wavefront holds 16 F x 16 F of the result.  Forward and backward: WJ
+// wavefronts side by side, 4 / WJ above each other, each summing all of K in
+// steps of 32 in ascending order.
 // Weights: K is the batch, the longest index, and the result the smallest,
 // so the block's KW wavefronts split K and add their parts in LDS in a fixed
 // order.  The bias gradient sums A's FP32 values before they are rounded.
-template <bool BF16, int EPI, int F, int KW>
+template <bool BF16, int EPI, int F, int WJ, int KW>
 __global__ __launch_bounds__(EPI == EPI_WEIGHTS ? 64 * KW : 256) void mlp_product_kernel(
     MlpProduct p) {
   constexpr bool TA = EPI == EPI_WEIGHTS, TB = EPI != EPI_FORWARD;
-  constexpr int G = F == 1 ? 4 : 2, WQ = EPI == EPI_WEIGHTS ? 1 : 2;
+  constexpr int G = F == 1 ? 4 : F == 2 ? 2 : 1;
+  constexpr int WI = EPI == EPI_WEIGHTS ? 1 : 4 / WJ;
   constexpr int TW = 16 * F;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, kq = lane >> 4;
-  const int i0 = (blockIdx.y * WQ + (WQ == 2 ? wave >> 1 : 0)) * TW;
-  const int j0 = (blockIdx.x * WQ + (WQ == 2 ? wave & 1 : 0)) * TW;
+  const int i0 = (blockIdx.y * WI + (EPI == EPI_WEIGHTS ? 0 : wave / WJ)) * TW;
+  const int j0 = (blockIdx.x * WJ + (EPI == EPI_WEIGHTS ? 0 : wave % WJ)) * TW;
   // this wavefront's k: all, or its share in whole chunks
   int kb = 0, ke = p.K;
   if (EPI == EPI_WEIGHTS) {
@@ -338,25 +340,37 @@ static unsigned g1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 // Launch of a product.  A block's result is 32 x 32 (weights: 16 x 16) while
 // that gives up to 1024 blocks, four per CU; beyond, four times as large,
-// which halves what each multiply reads.
-template <bool BF16, int EPI, int F>
+// which halves what each multiply reads.  From 2048 blocks of 64 x 64 on a
+// wavefront holds 64 x 64 by itself, which halves it once more and still gives
+// every CU two blocks (width 256, forward of 65536 samples 319 us, with 32 x 32
+// a wavefront 519; of 16384, 1024 blocks, 141 us); up to 64 columns the
+// four wavefronts stand above each other.
+template <bool BF16, int EPI, int F, int WJ>
 static void launch_product(const MlpProduct &p, hipStream_t st) {
-  constexpr int KW = 8, T = EPI == EPI_WEIGHTS ? 16 * F : 32 * F;
-  const dim3 grid((p.N + T - 1) / T, (p.M + T - 1) / T);
-  hipLaunchKernelGGL((mlp_product_kernel<BF16, EPI, F, KW>), grid,
+  constexpr int KW = 8, TJ = 16 * F * WJ;
+  constexpr int TI = EPI == EPI_WEIGHTS ? 16 * F : 16 * F * (4 / WJ);
+  const dim3 grid((p.N + TJ - 1) / TJ, (p.M + TI - 1) / TI);
+  hipLaunchKernelGGL((mlp_product_kernel<BF16, EPI, F, WJ, KW>), grid,
                      dim3(EPI == EPI_WEIGHTS ? 64 * KW : 256), 0, st, p);
+}
+
+template <bool BF16, int EPI>
+static void product_of(const MlpProduct &p, hipStream_t st) {
+  constexpr int WJ = EPI == EPI_WEIGHTS ? 1 : 2, T = 16 * WJ;
+  auto blocks = [&](int t) {
+    return (int64_t)((p.N + t - 1) / t) * ((p.M + t - 1) / t);
+  };
+  if (blocks(T) <= 1024) return launch_product<BF16, EPI, 1, WJ>(p, st);
+  if constexpr (EPI != EPI_WEIGHTS)
+    if (blocks(64) >= 2048)
+      return p.N <= 64 ? launch_product<BF16, EPI, 4, 1>(p, st)
+                       : launch_product<BF16, EPI, 4, 2>(p, st);
+  launch_product<BF16, EPI, 2, WJ>(p, st);
 }
 
 template <int EPI>
 static void product(const Mlp &q, const MlpProduct &p, hipStream_t st) {
-  constexpr int T = EPI == EPI_WEIGHTS ? 16 : 32;
-  const int64_t blocks = (int64_t)((p.N + T - 1) / T) * ((p.M + T - 1) / T);
-  if (q.prec == 0)
-    blocks <= 1024 ? launch_product<true, EPI, 1>(p, st)
-                   : launch_product<true, EPI, 2>(p, st);
-  else
-    blocks <= 1024 ? launch_product<false, EPI, 1>(p, st)
-                   : launch_product<false, EPI, 2>(p, st);
+  q.prec == 0 ? product_of<true, EPI>(p, st) : product_of<false, EPI>(p, st);
 }
 
 static int ensure_cap(Mlp &q, int B) {
