@@ -199,7 +199,7 @@ int rm_sweep_energies(const rm_sym_t *syms, int32_t n_sym, int32_t n_target,
  * cannot allocate: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments, results and errors as
  * rm_sweep_energies.  Its workspace (the per-energy matching systems, the
- * channel slots, the pole-sum work tables and counters) lives in one static
+ * channel slots, the pole-sum work tables) lives in one static
  * device array of RM_NOALLOC_SCRATCH_BYTES, which every GPU the library
  * runs on holds until the process ends; the mesh is swept in chunks of as
  * many energies as that array holds (about 240 at 200 channels), so large
@@ -207,7 +207,7 @@ int rm_sweep_energies(const rm_sym_t *syms, int32_t n_sym, int32_t n_target,
  * Differences: RM_FLAG_AUTOTUNE returns RM_ERR_ARG (timing allocates); the
  * pair form of the pole sum is used only where its products are already
  * resident (formed by an earlier allocating call), else the scaled-W
- * kernels; symmetries whose single energy (or whose tables and counters)
+ * kernels; symmetries whose single energy (or whose tables)
  * do not fit return RM_ERR_ARG.  The call synchronises `stream` once, after
  * copying its tables into the array, then enqueues the sweep.  Every call
  * on a GPU shares that GPU's array and leaves its contents behind: calls

@@ -9,10 +9,15 @@
 // points instead of at 128 energies, and each energy's R is the interpolant
 // plus the few poles within 6 h.  At 200 channels, 8000 poles and a mesh step
 // of 2e-4 that is 31 + 3 of 250 chunks' work per 16 energies.  The node values
-// are sums of the same products in the same order as a direct sum, and the
-// interpolation weights' squares sum to at most about one, so rounding is that
-// of the direct sum.  Groups are cut on the whole mesh, not on the chunk, so
-// results do not depend on the chunk length.
+// are sums of the same products in the same order as a direct sum; the squares
+// of an energy's 16 weights sum to 1 on average and to less than 2 at the ends
+// of the group, their magnitudes to less than 2.73.  So the far part is rounded
+// like a direct sum of it, up to 1.4 times that at the ends, while the near part
+// is shorter: against 80-bit sums R is off by 2.3e-15 (relative rms) where the
+// direct kernel is off by 5.2e-15 (200 channels, 12400 damped poles).
+// Groups are cut on the whole mesh, not on the chunk, so results do not depend
+// on the chunk length; an energy's last bits do depend on its group, so on the
+// energies beside it.
 //
 // Groups whose energies are not close together (unsorted, coarse, not finite)
 // or too few to pay for 16 points are left to the direct kernel, which runs

@@ -235,29 +235,15 @@ __device__ void ps_mixed_item(const SymDev &S, int IB, int JB0, int grp,
 template <bool BF16, int JMAX, int EW>
 __global__ __launch_bounds__(256) void polesum_mixed_kernel(PsLaunch L) {
   __shared__ MxSmem<BF16, JMAX, EW> sm;
-  __shared__ int s_item;
-  const int tid = threadIdx.x;
-  int it = -1;
-  if (!L.counter) {
-    const int chunk = (L.n_items + 7) / 8;
-    it = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
-  }
-  for (;;) {
-    if (L.counter) {
-      if (tid == 0) s_item = atomicAdd(L.counter, 1);
-      __syncthreads();
-      it = s_item;
-      __syncthreads();
-    }
-    if (it >= L.n_items) break;
-    const PsItem item = L.items[it];
-    const SymDev &S = L.syms[item.sym];
-    ps_mixed_item<BF16, JMAX, EW>(S, item.x, item.y, item.grp, L.E, L.m,
-                                  L.delta, L.band,
-                                  L.out.out + L.out.off[item.sym],
-                                  L.out.estride, L.out.ld_mult * S.n, sm);
-    if (!L.counter) break;
-  }
+  const int chunk = (L.n_items + 7) / 8;
+  const int it = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  if (it >= L.n_items) return;
+  const PsItem item = L.items[it];
+  const SymDev &S = L.syms[item.sym];
+  ps_mixed_item<BF16, JMAX, EW>(S, item.x, item.y, item.grp, L.E, L.m,
+                                L.delta, L.band,
+                                L.out.out + L.out.off[item.sym],
+                                L.out.estride, L.out.ld_mult * S.n, sm);
 }
 
 template <bool BF16>
@@ -284,11 +270,7 @@ static hipError_t launch_mx(const PsLaunch &L, int variant, dim3 grid,
 
 hipError_t launch_polesum_mixed(const PsLaunch &L, int variant,
                                 hipStream_t st) {
-  unsigned grid;
-  if (L.counter)
-    grid = (unsigned)std::max(1, std::min(L.grid, L.n_items));
-  else
-    grid = (unsigned)(8 * ((L.n_items + 7) / 8));
+  const unsigned grid = (unsigned)(8 * ((L.n_items + 7) / 8));
   if (L.prec == RM_PREC_BF16X3) return launch_mx<true>(L, variant, dim3(grid), st);
   return launch_mx<false>(L, variant, dim3(grid), st);
 }

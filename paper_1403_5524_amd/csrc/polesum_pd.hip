@@ -389,36 +389,18 @@ __device__ void pd_item(const SymDev &S, int pb, int grp,
 template <int PREC>
 __global__ __launch_bounds__(256) void polesum_pd_kernel(PsLaunch L) {
   __shared__ PdSmem<PREC> sm;
-  __shared__ int s_item;
-  const int tid = threadIdx.x;
-  int it = -1;
-  if (!L.counter) {
-    const int chunk = (L.n_items + 7) / 8;
-    it = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
-  }
-  for (;;) {
-    if (L.counter) {
-      if (tid == 0) s_item = atomicAdd(L.counter, 1);
-      __syncthreads();
-      it = s_item;
-      __syncthreads();
-    }
-    if (it >= L.n_items) break;
-    const PsItem item = L.items[it];
-    const SymDev &S = L.syms[item.sym];
-    pd_item<PREC>(S, item.x, item.grp, L.E, L.m, L.delta, L.band,
-                  L.out.out + L.out.off[item.sym], L.out.estride,
-                  L.out.ld_mult * S.n, sm);
-    if (!L.counter) break;
-  }
+  const int chunk = (L.n_items + 7) / 8;
+  const int it = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  if (it >= L.n_items) return;
+  const PsItem item = L.items[it];
+  const SymDev &S = L.syms[item.sym];
+  pd_item<PREC>(S, item.x, item.grp, L.E, L.m, L.delta, L.band,
+                L.out.out + L.out.off[item.sym], L.out.estride,
+                L.out.ld_mult * S.n, sm);
 }
 
 hipError_t launch_polesum_pd(const PsLaunch &L, hipStream_t st) {
-  unsigned grid;
-  if (L.counter)
-    grid = (unsigned)std::max(1, std::min(L.grid, L.n_items));
-  else
-    grid = (unsigned)(8 * ((L.n_items + 7) / 8));
+  const unsigned grid = (unsigned)(8 * ((L.n_items + 7) / 8));
   if (L.prec == RM_PREC_BF16X3)
     hipLaunchKernelGGL(polesum_pd_kernel<RM_PREC_BF16X3>, dim3(grid), dim3(256),
                        0, st, L);
@@ -624,35 +606,17 @@ __device__ void pd64_item(const SymDev &S, int pb, int grp,
 
 __global__ __launch_bounds__(256) void polesum_pd64_kernel(PsLaunch L) {
   __shared__ Pd64Smem sm;
-  __shared__ int s_item;
-  const int tid = threadIdx.x;
-  int it = -1;
-  if (!L.counter) {
-    const int chunk = (L.n_items + 7) / 8;
-    it = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
-  }
-  for (;;) {
-    if (L.counter) {
-      if (tid == 0) s_item = atomicAdd(L.counter, 1);
-      __syncthreads();
-      it = s_item;
-      __syncthreads();
-    }
-    if (it >= L.n_items) break;
-    const PsItem item = L.items[it];
-    const SymDev &S = L.syms[item.sym];
-    pd64_item(S, item.x, item.grp, L.E, L.m, L.out.out + L.out.off[item.sym],
-              L.out.estride, L.out.ld_mult * S.n, sm);
-    if (!L.counter) break;
-  }
+  const int chunk = (L.n_items + 7) / 8;
+  const int it = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  if (it >= L.n_items) return;
+  const PsItem item = L.items[it];
+  const SymDev &S = L.syms[item.sym];
+  pd64_item(S, item.x, item.grp, L.E, L.m, L.out.out + L.out.off[item.sym],
+            L.out.estride, L.out.ld_mult * S.n, sm);
 }
 
 hipError_t launch_polesum_pd64(const PsLaunch &L, hipStream_t st) {
-  unsigned grid;
-  if (L.counter)
-    grid = (unsigned)std::max(1, std::min(L.grid, L.n_items));
-  else
-    grid = (unsigned)(8 * ((L.n_items + 7) / 8));
+  const unsigned grid = (unsigned)(8 * ((L.n_items + 7) / 8));
   hipLaunchKernelGGL(polesum_pd64_kernel, dim3(grid), dim3(256), 0, st, L);
   return hipGetLastError();
 }

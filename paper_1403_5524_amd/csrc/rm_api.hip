@@ -1150,7 +1150,6 @@ static int plan_enqueue(Plan &p, hipStream_t st) {
         L.syms = p.d_syms;
         L.items = set.d_items[t];
         L.n_items = set.n_items[t];
-        L.counter = nullptr;
         L.E = p.E + c0;
         L.m = (int)m;
         L.e_off = c0;

@@ -202,14 +202,11 @@ hipError_t launch_chanfn(const Sym &s, const double *E, int64_t m,
 // span several symmetries.  FP64 variants use MFMA over every pole; mixed
 // variants use FP32 or split-BF16 MFMA over the far poles, |E_k - E| >=
 // band, and add the near tier (|E_k - E| < delta, FP64 operands) and the
-// band tier (FP32 operands, FP64 products and sum) in their epilogues.  With a counter (device int
-// holding 0) the grid is persistent and pulls items from it.
+// band tier (FP32 operands, FP64 products and sum) in their epilogues.
 struct PsLaunch {
   const SymDev *syms;
   const PsItem *items;
   int n_items;
-  int *counter;         // nullable
-  int grid;             // persistent grid size (used with counter)
   const double *E;
   int m;
   int64_t e_off, m_all; // E[-e_off .. m_all - e_off) is the whole mesh
