@@ -92,3 +92,35 @@ def test_damped_photoionization_of_refused_meshes(n, nh, M, kind):
     err = np.abs(sig.cpu().numpy() - ref).max() / np.abs(ref).max()
     log("damped %s n=%d M=%d: %.2e" % (kind, n, M, err))
     assert err < 1e-6
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+def test_energies_that_are_not_finite(bad):
+    """They spoil no other energy of their group, and have no open channel or
+    no finite result."""
+    import torch
+    from paper_1403_5524_amd import native, workloads as wl
+    n, M = 17, 200
+    s = wl.tiny(n=n, n_poles=600, M=8, seed=3).syms[0]
+    E = 2.5 + 1e-4 * (np.arange(M) + 0.5)
+    ref = E.copy()
+    at = [0, 63, 130]
+    E[at] = bad
+    keep = np.setdiff1d(np.arange(M), at)
+    h = native.load_symmetry(s)
+    R = native.rm_rmatrix(h, torch.as_tensor(E, device="cuda:0")).cpu().numpy()
+    om, st = native.rm_sweep_energies([h], n, torch.as_tensor(E, device="cuda:0"))
+    good, gst = native.rm_sweep_energies([h], n, torch.as_tensor(ref, device="cuda:0"))
+    h.free()
+    p, w = s.E_pole, np.asarray(s.w)
+    for e in keep:
+        d = 1.0 / (p - E[e])
+        exact = (w * d) @ w.T / (2 * s.a)
+        mag = (np.abs(w) * np.abs(d)) @ np.abs(w).T / (2 * s.a)
+        assert (np.abs(R[e] - exact) / mag).max() < 2 * (p.size + 64) * 2.0 ** -53
+    om, good = om.cpu().numpy(), good.cpu().numpy()
+    err = np.abs(om - good)[keep].max() / np.abs(good).max()
+    log("%s: others off by %.1e, status there %s" % (bad, err, st.cpu().numpy()[at]))
+    assert err < 1e-6
+    assert np.array_equal(st.cpu().numpy()[keep], gst.cpu().numpy()[keep])
+    assert (st.cpu().numpy()[at] != 0).all()
