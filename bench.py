@@ -48,32 +48,37 @@ PREC_CODE = {"fp64": 0, "fp32": 1, "bf16x3": 2}
 # HBM bytes per energy from two rocprofv3 --pmc runs (FETCH_SIZE, then
 # WRITE_SIZE) of the 200-channel workload, scaled by what the same counters
 # read for a plain 1 GiB device copy (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0).
-# A figure applies only while its kernel source is the one measured.
+# A figure applies only while its kernels' sources (csrc/) are those measured.
 PMC_TRAFFIC = {
-    "match_kernel": {"src": "paper_1403_5524_amd/csrc/match.hip",
-                     "sha256_16": "87d60d344558c9f6",
-                     "bytes_per_energy": 23.20e6 + 7.640e6},
-    "polesum_fp64": {"src": "paper_1403_5524_amd/csrc/polesum.hip",
-                     "sha256_16": "63e41f950c81571c",
-                     "bytes_per_energy": 0.1942e6 + 0.3228e6},
-    "polesum_bf16x3": {"src": "paper_1403_5524_amd/csrc/polesum_pd.hip",
-                       "sha256_16": "045eb073247d461b",
-                       "bytes_per_energy": 0.2359e6 + 0.7140e6},
-    "polesum_fp32": {"src": "paper_1403_5524_amd/csrc/polesum_pd.hip",
-                     "sha256_16": "045eb073247d461b",
-                     "bytes_per_energy": 0.2357e6 + 0.7133e6},
+    "matching": {"src": ("match_core.h", "team.h"),
+                 "sha256_16": "00b8602ba59eb40f",
+                 "bytes_per_energy": 12.87e6 + 7.260e6},
+    "polesum_fp64": {"src": ("polesum_group.h", "polesum_group.hip",
+                             "polesum.hip"),
+                     "sha256_16": "fa3c7e099ee2cd3c",
+                     "bytes_per_energy": 0.0940e6 + 0.3263e6},
+    "polesum_bf16x3": {"src": ("polesum_pd.hip",),
+                       "sha256_16": "848cc3391d82bcf2",
+                       "bytes_per_energy": 0.2356e6 + 0.7280e6},
+    "polesum_fp32": {"src": ("polesum_pd.hip",),
+                     "sha256_16": "848cc3391d82bcf2",
+                     "bytes_per_energy": 0.2848e6 + 0.6747e6},
 }
 
 
 def measured_traffic(key, energies):
-    """HBM bytes for `energies` energies, or None if the kernel changed."""
+    """HBM bytes for `energies` energies, or None if the kernels changed."""
     import hashlib
     t = PMC_TRAFFIC.get(key)
     if t is None:
         return None
-    with open(os.path.join(ROOT, t["src"]), "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest()[:16] != t["sha256_16"]:
-            return None
+    sha = hashlib.sha256()
+    for name in t["src"]:
+        with open(os.path.join(ROOT, "paper_1403_5524_amd", "csrc", name),
+                  "rb") as f:
+            sha.update(f.read())
+    if sha.hexdigest()[:16] != t["sha256_16"]:
+        return None
     return t["bytes_per_energy"] * energies
 
 
@@ -90,8 +95,8 @@ def match_flops(n, n_open):
 
 
 def match_flops_executed(n, n_open):
-    """The flops the kernel runs at most energies: the LU (2 n^3 / 3 instead
-    of n^3/3), the substitutions (2 n^2 m) and its T step (3 m^3: lower
+    """The flops that run at most energies: the LU (2 n^3 / 3 instead of
+    n^3/3), the substitutions (2 n^2 m) and the T step (3 m^3: lower
     triangle of 1 + K^2 m^3, Cholesky m^3/3, L^-1 m^3/3, A = L^-T L^-1
     m^3/3, lower triangle of Y = K A m^3; energies with large K take a
     route of 13 m^3 / 3)."""
@@ -670,8 +675,7 @@ def main():
         for key, flops, peak, stg, tkey in (
                 ("polesum_%s" % prec, flops_step, PEAK[prec], "polesum",
                  "polesum_%s" % prec),
-                ("match_kernel", mflops_step, PEAK["fp64"], "match",
-                 "match_kernel")):
+                ("matching", mflops_step, PEAK["fp64"], "match", "matching")):
             ms_tot, launches = stage[stg]
             lp = launches / steps if launches else 0
             ach = (flops * steps / (ms_tot * 1e-3) / 1e12
@@ -684,16 +688,17 @@ def main():
                 "flops_per_launch": flops / lp if lp else None,
                 "avg_launch_ms": ms_tot / launches if launches else None,
                 "ms_per_step": ms_tot / steps}
-        mk = kernels["match_kernel"]
+        mk = kernels["matching"]
         if mk["achieved"]:
-            # the flops the kernel runs: its LU does 2n^3/3 where the minimal
-            # count has the n^3/3 of a symmetric factorisation, its T step
+            # the flops that run: the LU does 2n^3/3 where the minimal
+            # count has the n^3/3 of a symmetric factorisation, the T step
             # 3 n_o^3 where the minimal count has 16 n_o^3/3
             mk["achieved_executed_flops"] = mk["achieved"] * mflops_exec / mflops_step
             mk["flops_note"] = ("achieved counts n^3/3 + 2 n^2 n_o + 16 n_o^3/3 "
                                 "per energy; achieved_executed_flops counts "
-                                "2 n^3/3 + 2 n^2 n_o + 3 n_o^3, what the "
-                                "kernel runs")
+                                "2 n^3/3 + 2 n^2 n_o + 3 n_o^3, what runs; a "
+                                "launch is one chunk's assembly, LU, T step "
+                                "and large-K solves")
         ps = kernels["polesum_%s" % prec]
         if prec == "fp64" and ps["achieved"]:
             ps["flops_note"] = ("the direct sum's n (n + 1) N_H per energy; far "

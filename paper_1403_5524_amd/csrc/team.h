@@ -8,12 +8,12 @@
 //
 // What bounds it: at one wavefront per energy, two per SIMD, 2048 energies
 // were in flight and their 0.96 MB workspaces (200 channels) streamed through
-// HBM between the block steps: 30.8 MB and 6.0 us per energy.  A team keeps a
-// quarter or an eighth as many energies in flight, reads each panel once per
-// team through the CU's own cache, and spreads the serial phases (pivot
-// search, diagonal blocks) over as many SIMDs: 8.7 MB and 3.9 us per energy
-// (LU 2.1, T step 1.5, assembly 0.3) at 4096 energies, 2.4 TB/s in the LU where
-// a copy reaches 4.3.
+// HBM between the block steps: 30.8 MB and 6.6 us per energy with all channels
+// open.  A team keeps a quarter or an eighth as many energies in flight, reads
+// each panel once per team through the CU's own cache, and spreads the serial
+// phases (pivot search, diagonal blocks) over as many SIMDs: 20.1 MB and 5.2 us
+// (LU 2.3, T step 2.5, assembly 0.3) at 8192 energies.  The LU and the T step
+// then move 3.9 TB/s, where a copy reaches 4.3.
 //
 // Every pass over memory is written as "issue all loads of a batch, then
 // compute, then store": the compiler cannot move a load above a store it
