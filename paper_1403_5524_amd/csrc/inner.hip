@@ -413,8 +413,11 @@ __global__ __launch_bounds__(256) void bj_rotate_kernel(
 
 // Rotations of a round.  Four row groups a wave share the loads of U; one a
 // wave, with four times the wavefronts, where four would leave fewer than
-// four workgroups per CU (dimension 1024: 8.1 us a round against 10.2 with
-// four groups and both matrices per wave).
+// four workgroups per CU, which is below dimension 2048.  The Jacobi stage with
+// one and with four: dimension 512 8.8 and 9.3 ms, 1024 21.9 and 21.8, 1792 53.7
+// and 53.8, 2048 71.8 and 70.2, 3072 171.6 and 170.5, 4096 411 and 367.  (Four
+// groups and both matrices per wave, at dimension 1024: 10.2 us a round, now
+// 7.8.)
 static void launch_rotate(double *A, double *V, int Dp, int nb, int t,
                           const double *U, const int *skip, hipStream_t st) {
   const int npair = nb / 2;
